@@ -367,8 +367,10 @@ ml2_status ml2_load_ensemble(const ml2_ensemble_desc *desc, ml2_ensemble **out) 
     (void)hipFree(f.d_trees);
     return hip_fail(e, "hipMemcpy");
   }
+  ml2::rank_load(views, &f);
   ml2_ensemble *h = new (std::nothrow) ml2_ensemble;
   if (!h) {
+    ml2::rank_free(&f);
     (void)hipFree(f.d_trees);
     return fail(ML2_ERR_OUT_OF_MEMORY, "handle allocation failed");
   }
@@ -382,6 +384,7 @@ void ml2_free_ensemble(ml2_ensemble *e) {
   int cur = 0;
   const bool other = hipGetDevice(&cur) == hipSuccess && cur != e->f.device;
   if (other) (void)hipSetDevice(e->f.device);
+  ml2::rank_free(&e->f);
   (void)hipFree(e->f.d_trees);
   if (other) (void)hipSetDevice(cur);
   delete e;

@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <vector>
+
 #include "layout.h"
 #include "ml2.h"
 
@@ -19,6 +21,17 @@ constexpr size_t kTreeSlack = 128 * 1024;  // readable zero bytes after the tree
 // once per kernel, device and size increase).
 hipError_t ensure_dynamic_lds(const void *fn, size_t bytes);
 
+// The rank form of an ensemble of perfect trees (rank_pack.h) on the device;
+// ok = 0: the ensemble has none.
+struct RankForm {
+  int32_t ok, mode, depth, group, waves, per_cu;  // waves of a workgroup, workgroups of a CU
+  int32_t pays;  // the walk saves more than ranking a row costs
+  int32_t nslots, nchunks, nlines;
+  uint32_t slot_bytes, tile_bytes;
+  void *block;  // one allocation holding every table below
+  const void *slots, *grid, *line_group, *groups, *group_slot, *chunks;
+};
+
 struct Forest {
   int device;
   int32_t num_trees;        // trees in the descriptor
@@ -30,6 +43,7 @@ struct Forest {
   float base;
   uint32_t rec_bytes;       // record_bytes(depth), or record_bytes(0) when ragged
   void *d_trees;            // records * rec_bytes bytes (+ kTreeSlack zero bytes)
+  RankForm rank;            // perfect trees only
 };
 
 // Launch parameters of a walk (chosen on the host from D and F).
@@ -42,6 +56,7 @@ struct WalkPlan {
   int nbuf;         // LDS chunk buffers: 2 (asynchronous refill) or 1
   size_t lds_bytes; // dynamic LDS per workgroup
   int grid;         // workgroups
+  int cus;          // compute units of the device
 };
 
 // Returns false (and sets *why) if no plan fits the LDS of one workgroup.
@@ -58,6 +73,20 @@ bool plan_fused(const Forest &v, const Forest &p, int64_t n, int64_t ld, const f
 hipError_t launch_fused(const Forest &v, const Forest &p, const WalkPlan &pl, int nv, int np,
                         const float *X, int64_t n, int64_t ld, uint8_t *valid_out,
                         float *margin_out, float *score_out, hipStream_t s);
+
+// Builds the rank form of `f` (perfect trees of `views`, F features) on the
+// current device; without one (too many thresholds, no fitting slot, no
+// memory) f->rank.ok stays 0 and the float walks take every call.
+struct TreeView;
+void rank_load(const std::vector<TreeView> &views, Forest *f);
+void rank_free(Forest *f);
+// Whether a walk of n_work rows (perf: the performance walk) takes the rank form.
+bool rank_takes(const Forest &f, int64_t n_work, int cu_count, bool perf);
+hipError_t launch_rank_validity(const Forest &f, const float *X, int64_t n, int64_t ld,
+                                uint8_t *valid_out, float *margin_out, int cu_count,
+                                hipStream_t s);
+hipError_t launch_rank_perf(const Forest &f, const float *X, int64_t n, int64_t ld,
+                            const uint8_t *valid, float *score_out, int cu_count, hipStream_t s);
 
 // Tuning overrides (ml2_tune_walk_plan / ml2_tune_layout): process-wide,
 // zero = the planner's or loader's choice.

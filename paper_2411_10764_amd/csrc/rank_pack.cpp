@@ -1,0 +1,374 @@
+// Host side of the rank form (rank_pack.h).
+#include "rank_pack.h"
+
+#include <math.h>
+#include <string.h>
+
+#include <algorithm>
+
+namespace ml2 {
+namespace {
+
+uint32_t bits_of(float v) {
+  uint32_t b;
+  memcpy(&b, &v, 4);
+  return b;
+}
+
+float float_of(uint32_t b) {
+  float v;
+  memcpy(&v, &b, 4);
+  return v;
+}
+
+// Order-preserving key of a threshold; -0.0 and +0.0 are the same threshold.
+uint32_t key_of(float t) {
+  const uint32_t b = bits_of(t == 0.0f ? 0.0f : t);
+  return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
+}
+
+float value_of(uint32_t key) {
+  return float_of((key & 0x80000000u) ? (key & 0x7FFFFFFFu) : ~key);
+}
+
+struct Entry {
+  uint32_t key, node;
+};
+
+// Thresholds of one feature: a code, the padding of its last segment
+// included, fits 16 bits.
+constexpr size_t kMostThresholds = 65535 - 8192;
+
+// Stable LSD radix sort by key (11-bit digits); short lists by comparison.
+void sort_entries(Entry *e, Entry *tmp, size_t n) {
+  if (n < 2048) {
+    std::sort(e, e + n, [](const Entry &a, const Entry &b) { return a.key < b.key; });
+    return;
+  }
+  constexpr int B = 11;
+  for (int pass = 0; pass < 3; ++pass) {
+    uint32_t count[1 << B] = {0};
+    const int sh = pass * B;
+    for (size_t i = 0; i < n; ++i) ++count[(e[i].key >> sh) & ((1u << B) - 1)];
+    uint32_t at = 0;
+    for (uint32_t &c : count) {
+      const uint32_t k = c;
+      c = at;
+      at += k;
+    }
+    for (size_t i = 0; i < n; ++i) tmp[count[(e[i].key >> sh) & ((1u << B) - 1)]++] = e[i];
+    std::swap(e, tmp);
+  }
+  memcpy(tmp, e, n * sizeof(Entry));  // three passes end in the other buffer
+}
+
+// The grid of a sorted list of distinct thresholds: multiples of a power of
+// two h <= 1 whose range holds at most `most` points.  h is not above 1, so
+// x / h never rounds towards zero (no underflow) and floor(x / h) < t / h
+// exactly when x < t; overflow to infinity keeps the order.
+bool find_grid(const std::vector<float> &t, int most, RankGrid *g) {
+  int e = 0;  // h = 2^e
+  for (float v : t) {
+    if (!std::isfinite(v)) return false;
+    if (v == 0.0f) continue;
+    int x;
+    const double m = frexp((double)v, &x);  // v = m * 2^x, m a multiple of 2^-24
+    const int64_t q = (int64_t)ldexp(m, 24);
+    int low = x - 24;
+    for (int64_t w = q < 0 ? -q : q; (w & 1) == 0; w >>= 1) ++low;
+    if (low < e) e = low;
+  }
+  if (e < -100) return false;
+  const double lo = ldexp((double)t.front(), -e), hi = ldexp((double)t.back(), -e);
+  if (fabs(lo) > 4194304.0 || fabs(hi) > 4194304.0 || hi - lo + 1.0 > (double)most) return false;
+  g->scale = (float)ldexp(1.0, -e);
+  g->bias = (float)(1.0 - lo);
+  g->top = (float)(hi - lo + 1.0);
+  return true;
+}
+
+// The node of a split: its feature's half-word and the comparand of code t.
+uint32_t node_word(const RankCodes &c, int feat, uint32_t t) {
+  const RankField &fd = c.field[(size_t)feat];
+  if (c.mode != kRankPacked) return (fd.off << 16) | t;
+  const uint32_t s = 16u - fd.low - fd.width, T = t << (16 - fd.width);
+  return (fd.off << 16) | (s ? T - 16u + s : T);
+}
+
+// Rows of a tile of one byte per feature up to which sixteen waves' tiles
+// leave room for a slot of trees (64 features).
+constexpr uint32_t kMostByteRows = 16;
+
+// The mode of a tile whose features have codes[f] codes above 0, and the
+// features' places in it.
+void place_fields(const std::vector<size_t> &codes, RankCodes *out) {
+  size_t most = 0;
+  uint32_t used = 0;
+  for (size_t c : codes) {
+    most = std::max(most, c);
+    used += c != 0;
+  }
+  out->mode = most > 4095 ? kRankHalf
+              : most <= 255 && used <= 4 * kMostByteRows ? kRankByte
+                                                         : kRankPacked;
+  std::vector<int> by_width[3];  // 4, 8, 12 bits
+  uint32_t half = 0;             // half-words used
+  auto at = [&](uint32_t h) { return (h >> 1) * kRankRow + (h & 1) * 2u; };
+  uint32_t n = 0;
+  for (size_t f = 0; f < codes.size(); ++f) {
+    out->field[f] = RankField{0, 0, 0};
+    if (codes[f] == 0) continue;
+    if (out->mode == kRankByte) {
+      out->field[f] = RankField{(n >> 2) * kRankRow + (n & 3), 0, 8};
+      ++n;
+      half = (n + 1) / 2;
+    } else if (out->mode == kRankHalf) {
+      out->field[f] = RankField{at(half++), 0, 16};
+    } else {
+      by_width[codes[f] <= 15 ? 0 : codes[f] <= 255 ? 1 : 2].push_back((int)f);
+    }
+  }
+  size_t n4 = 0;  // 4-bit features placed
+  auto put = [&](int f, int low, int width) {
+    out->field[(size_t)f] = RankField{at(half), (uint8_t)low, (uint8_t)width};
+  };
+  auto put4 = [&](int low) {
+    if (n4 < by_width[0].size()) put(by_width[0][n4++], low, 4);
+  };
+  for (int f : by_width[2]) {
+    put(f, 4, 12);
+    put4(0);
+    ++half;
+  }
+  for (size_t i = 0; i < by_width[1].size(); ++half) {
+    put(by_width[1][i++], 8, 8);
+    if (i < by_width[1].size()) {
+      put(by_width[1][i++], 0, 8);
+    } else {
+      put4(4);
+      put4(0);
+    }
+  }
+  for (; n4 < by_width[0].size(); ++half)
+    for (int low : {12, 8, 4, 0}) put4(low);
+  out->rows = std::max<uint32_t>(1, (half + 1) / 2);
+}
+
+// Levels of the smallest perfect search tree of n thresholds.
+int steps_of(size_t n) {
+  int s = 1;
+  while (n >> s) ++s;
+  return s;
+}
+
+// n sorted thresholds as a search tree of s levels, breadth-first from entry
+// 1, padded with +inf.
+void put_search_tree(const float *t, size_t n, int s, char *dst) {
+  const size_t size = (size_t)1 << s;
+  for (size_t u = 1; u < size; ++u) {
+    const int l = steps_of(u) - 1;  // its level
+    const size_t in_order = (((u - ((size_t)1 << l)) * 2 + 1) << (s - 1 - l)) - 1;
+    const float v = in_order < n ? t[in_order] : INFINITY;
+    memcpy(dst + 4 * u, &v, 4);
+  }
+}
+
+// One tree of the rank form; leaves above depth D are replicated.
+void put_tree(const TreeView &tv, const RankCodes &codes, const uint16_t *code, int D,
+              char *dst) {
+  const int K = rank_top(D);
+  struct Item {
+    int32_t node;
+    int level;
+    uint32_t idx;
+  };
+  std::vector<Item> stack;
+  stack.push_back({0, 0, 0u});
+  while (!stack.empty()) {
+    const Item it = stack.back();
+    stack.pop_back();
+    const bool leaf = tv.left[it.node] == -1 && tv.right[it.node] == -1;
+    if (it.level == D) {
+      const uint32_t w = bits_of(tv.val[it.node]);
+      memcpy(dst + 4 * ((size_t)(1u << D) + it.idx), &w, 4);
+      continue;
+    }
+    const uint32_t at = it.level < K
+                            ? (it.idx << (K - it.level)) + (1u << (K - 1 - it.level))
+                            : (1u << it.level) + it.idx;
+    // a replicated leaf: nothing is below 0, and both sides hold it
+    const uint32_t w = leaf ? 0u : node_word(codes, tv.feat[it.node], code[it.node]);
+    memcpy(dst + 4 * (size_t)at, &w, 4);
+    const int32_t l = leaf ? it.node : tv.left[it.node], r = leaf ? it.node : tv.right[it.node];
+    stack.push_back({l, it.level + 1, 2 * it.idx + 1});
+    stack.push_back({r, it.level + 1, 2 * it.idx});
+  }
+}
+
+}  // namespace
+
+bool rank_codes(const std::vector<TreeView> &views, int num_features, RankCodes *out) {
+  const size_t F = (size_t)num_features;
+  size_t nodes = 0;
+  std::vector<size_t> first(F + 1, 0);
+  for (const TreeView &tv : views) {
+    for (int64_t i = 0; i < tv.size; ++i)
+      if (tv.left[i] != -1) ++first[(size_t)tv.feat[i] + 1];
+    nodes += (size_t)tv.size;
+  }
+  if (nodes > 0xFFFFFFFFull) return false;
+  for (size_t f = 0; f < F; ++f) first[f + 1] += first[f];
+  std::vector<Entry> all(first[F]), tmp(first[F]);
+  std::vector<size_t> at(first.begin(), first.end() - 1);
+  uint32_t base = 0;
+  for (const TreeView &tv : views) {
+    for (int64_t i = 0; i < tv.size; ++i)
+      if (tv.left[i] != -1)
+        all[at[(size_t)tv.feat[i]]++] = {key_of(tv.thr[i]), base + (uint32_t)i};
+    base += (uint32_t)tv.size;
+  }
+  out->code.assign(nodes, 0);
+  out->table.assign(F, {});
+  out->grid.assign(F, RankGrid{0.0f, 0.0f, 0.0f, 0u});
+  out->field.assign(F, RankField{0, 0, 0});
+  std::vector<size_t> codes(F, 0);
+  for (size_t f = 0; f < F; ++f) {
+    const size_t n = first[f + 1] - first[f];
+    if (n == 0) continue;
+    Entry *e = all.data() + first[f];
+    sort_entries(e, tmp.data() + first[f], n);
+    std::vector<float> &t = out->table[f];
+    for (size_t i = 0; i < n; ++i)
+      if (i == 0 || e[i].key != e[i - 1].key) t.push_back(value_of(e[i].key));
+    if (t.size() > kMostThresholds) return false;
+    RankGrid g{};
+    // a grid whose codes take no wider a field than the table's would, or
+    // that a byte holds (a table costs a search)
+    const size_t n_t = t.size();
+    const bool grid = find_grid(t, n_t <= 255 ? 255 : n_t <= 4095 ? 4095 : 65535, &g);
+    size_t j = 0;
+    for (size_t i = 0; i < n; ++i) {
+      if (i && e[i].key != e[i - 1].key) ++j;
+      out->code[e[i].node] =
+          (uint16_t)(grid ? (int64_t)((double)t[j] * g.scale + g.bias) : (int64_t)j + 1);
+    }
+    codes[f] = grid ? (size_t)g.top : t.size();
+    if (grid) {
+      out->grid[f] = g;
+      t.clear();
+    }
+  }
+  place_fields(codes, out);
+  return true;
+}
+
+bool rank_pack(const std::vector<TreeView> &views, const RankCodes &codes, int num_features,
+               int D, int group, uint32_t slot_bytes, RankPack *out) {
+  const uint32_t RB = rank_tree_bytes(D);
+  if (slot_bytes % 16 || (uint64_t)group * RB > slot_bytes) return false;
+  out->mode = codes.mode;
+  out->rows = codes.rows;
+  out->group = group;
+  out->lines = (num_features + kRankLine - 1) / kRankLine;
+  out->grid.assign((size_t)out->lines * kRankLine, RankGrid{0.0f, 0.0f, 0.0f, 0u});
+  uint32_t fill = 0;  // bytes used of the last slot
+  auto slot = [&](int s) { return out->data.data() + (size_t)s * slot_bytes; };
+  auto new_slot = [&]() {
+    out->data.resize(out->data.size() + slot_bytes, 0);
+    ++out->slots;
+    fill = 0;
+  };
+  new_slot();
+  // the order in which the kernels write codes, and so which of a dword's
+  // fields comes first: per line the grid features, then the groups
+  std::vector<uint8_t> written(codes.rows, 0);
+  auto put_of = [&](int f, bool again) {
+    const RankField &fd = codes.field[(size_t)f];
+    const uint32_t dword = fd.off & ~3u, bit = (fd.off & 3u) * 8u + fd.low;
+    uint8_t &w = written[dword / kRankRow];
+    const uint32_t put = dword | (bit << 16) | ((w || again) ? kRankAdd : 0u);
+    w = 1;
+    return put;
+  };
+  for (int l = 0; l < out->lines; ++l) {
+    out->line_group.push_back((int32_t)out->groups.size());
+    std::vector<int> search;
+    for (int f = l * kRankLine; f < std::min(num_features, (l + 1) * kRankLine); ++f) {
+      if (codes.grid[(size_t)f].top != 0.0f) {
+        out->grid[(size_t)f] = codes.grid[(size_t)f];
+        out->grid[(size_t)f].put = put_of(f, false);
+      } else if (!codes.table[(size_t)f].empty()) {
+        search.push_back(f);
+      }
+    }
+    // tables of like sizes next to one another, so that they share groups
+    std::stable_sort(search.begin(), search.end(), [&](int a, int b) {
+      return codes.table[(size_t)a].size() < codes.table[(size_t)b].size();
+    });
+    int in_group = 4, group_steps = 0;  // segments of the open group (4: none open)
+    for (int f : search) {
+      const std::vector<float> &t = codes.table[(size_t)f];
+      for (size_t done = 0; done < t.size();) {
+        size_t n = t.size() - done;
+        int steps = steps_of(n);
+        if (fill + (4u << steps) > slot_bytes) {
+          if (fill != 0) {
+            new_slot();
+            in_group = 4;
+          }
+          while ((4u << steps) > slot_bytes || steps > 13) --steps;
+          n = std::min(n, ((size_t)1 << steps) - 1);
+        }
+        if (in_group == 4 || group_steps != steps) {
+          out->groups.push_back(RankGroup{});
+          out->group_slot.push_back(out->slots - 1);
+          in_group = 0;
+          group_steps = steps;
+        }
+        RankSeg &s = out->groups.back().seg[in_group];
+        s.lane_reg = (uint32_t)(f % kRankLine);
+        s.put = put_of(f, done != 0);
+        s.table_off = fill;
+        s.steps = (uint32_t)steps;
+        for (int i = in_group + 1; i < 4; ++i) {  // repeats until another segment takes the place
+          out->groups.back().seg[i] = s;
+          out->groups.back().seg[i].put = kRankNone;
+        }
+        ++in_group;
+        put_search_tree(t.data() + done, n, steps, slot(out->slots - 1) + fill);
+        fill += 4u << steps;
+        done += n;
+        if (done < t.size()) {  // the rest in a slot and a group of its own
+          new_slot();
+          in_group = 4;
+        }
+      }
+    }
+  }
+  out->line_group.push_back((int32_t)out->groups.size());
+  fill = (fill + 127u) & ~127u;  // trees start on a bank row
+  size_t node0 = 0, t = 0;
+  const size_t total = (views.size() + group - 1) / group * group;
+  while (t < total) {
+    uint32_t fit = fill < slot_bytes ? (slot_bytes - fill) / RB / group * group : 0;
+    if (fit == 0) {
+      new_slot();
+      fit = slot_bytes / RB / group * group;
+    }
+    const size_t n = std::min<size_t>(fit, total - t);
+    out->chunks.push_back({out->slots - 1, (int32_t)fill, (int32_t)n, 0});
+    for (size_t i = 0; i < n; ++i, ++t, fill += RB) {
+      char *dst = slot(out->slots - 1) + fill;
+      if (t < views.size()) {
+        put_tree(views[t], codes, codes.code.data() + node0, D, dst);
+        node0 += (size_t)views[t].size;
+      } else {  // padding: every leaf -0.0 (x + (-0.0) == x)
+        const uint32_t z = 0x80000000u;
+        for (uint32_t j = 1u << D; j < 2u << D; ++j) memcpy(dst + 4 * (size_t)j, &z, 4);
+      }
+    }
+  }
+  return true;
+}
+
+}  // namespace ml2

@@ -1,0 +1,11 @@
+// The performance walks over the rank form (rank_walk.h).
+#include "rank_walk.h"
+
+namespace ml2 {
+
+hipError_t launch_rank_perf_kernel(int depth, RankMode mode, int group, int waves, const RankArgs &a,
+                                   int grid, size_t lds, hipStream_t s) {
+  return rank::launch<true>(depth, mode, group, waves, a, grid, lds, s);
+}
+
+}  // namespace ml2

@@ -1680,6 +1680,7 @@ bool try_plan(const Forest &f, int64_t n_work, int cu_count, int S, int W, int m
   if (wgs < grid) grid = wgs;
   if (grid < 1) grid = 1;
   q.grid = (int)grid;
+  q.cus = cu_count;
   *p = q;
   return true;
 }
@@ -1894,6 +1895,8 @@ bool plan_walk(const Forest &f, int64_t n_work, int cu_count, WalkPlan *p, const
 
 hipError_t launch_validity(const Forest &f, const WalkPlan &p, const float *X, int64_t n,
                            int64_t ld, uint8_t *valid_out, float *margin_out, hipStream_t s) {
+  if (rank_takes(f, n, p.cus, false))
+    return launch_rank_validity(f, X, n, ld, valid_out, margin_out, p.cus, s);
   WalkArgs a = make_args(f, p, X, n, ld);
   a.valid_out = valid_out;
   a.margin_out = margin_out;
@@ -1902,6 +1905,8 @@ hipError_t launch_validity(const Forest &f, const WalkPlan &p, const float *X, i
 
 hipError_t launch_perf(const Forest &f, const WalkPlan &p, const float *X, int64_t n,
                        int64_t ld, const uint8_t *valid, float *score_out, hipStream_t s) {
+  if (rank_takes(f, n, p.cus, true))
+    return launch_rank_perf(f, X, n, ld, valid, score_out, p.cus, s);
   WalkArgs a = make_args(f, p, X, n, ld);
   a.valid_in = valid;
   a.score_out = score_out;
