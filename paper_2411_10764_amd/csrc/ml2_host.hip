@@ -9,6 +9,8 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -16,6 +18,7 @@
 #include <vector>
 
 #include "ml2_internal.h"
+#include "host_parallel.h"
 #include "pack.h"
 
 using ml2::pack_ragged;
@@ -273,20 +276,38 @@ ml2_status ml2_load_ensemble(const ml2_ensemble_desc *desc, ml2_ensemble **out) 
   bool any_default_left = false;
   std::vector<TreeView> views((size_t)d.num_trees);
   std::vector<int> depths((size_t)d.num_trees);
+  // Trees are checked side by side; the first bad one is then checked again
+  // here for its message.
+  const int64_t T = d.num_trees;
+  std::vector<double> leaf_of((size_t)T, 0.0);
+  std::vector<uint8_t> bad((size_t)T, 0);
+  int64_t ranged = 0;  // trees before the first bad node range
+  for (; ranged < T; ++ranged) {
+    const int64_t a = d.tree_node_offset[ranged], b = d.tree_node_offset[ranged + 1];
+    if (b <= a || b - a > (int64_t)INT32_MAX) break;
+    views[(size_t)ranged] =
+        TreeView{d.left_child + a,      d.right_child + a,
+                 d.split_feature + a,   d.split_threshold + a,
+                 d.leaf_value + a,      d.default_left ? d.default_left + a : nullptr,
+                 b - a};
+  }
+  try {
+    ml2::parallel_for(ranged, ranged ? d.tree_node_offset[ranged] : 0, [&](int64_t t) {
+      bad[(size_t)t] = check_tree(d, (int32_t)t, views[(size_t)t], &depths[(size_t)t],
+                                  &leaf_of[(size_t)t]) != ML2_OK;
+    });
+  } catch (const std::bad_alloc &) {
+    return fail(ML2_ERR_OUT_OF_MEMORY, "host memory for checking the trees");
+  }
   for (int32_t t = 0; t < d.num_trees; ++t) {
-    const int64_t a = d.tree_node_offset[t], b = d.tree_node_offset[t + 1];
-    if (b <= a || b - a > (int64_t)INT32_MAX)
+    if (t == ranged)
       return fail(ML2_ERR_INVALID_ARG, "tree %d: node range [%lld, %lld) is empty or too large",
-                  t, (long long)a, (long long)b);
-    TreeView tv{d.left_child + a, d.right_child + a, d.split_feature + a,
-                d.split_threshold + a, d.leaf_value + a,
-                d.default_left ? d.default_left + a : nullptr, b - a};
-    int dt = 0;
-    ml2_status st = check_tree(d, t, tv, &dt, &max_leaf);
-    if (st != ML2_OK) return st;
-    if (dt > depth) depth = dt;
-    depths[(size_t)t] = dt;
-    views[(size_t)t] = tv;
+                  t, (long long)d.tree_node_offset[t], (long long)d.tree_node_offset[t + 1]);
+    const TreeView &tv = views[(size_t)t];
+    if (bad[(size_t)t])
+      return check_tree(d, t, tv, &depths[(size_t)t], &leaf_of[(size_t)t]);
+    depth = std::max(depth, depths[(size_t)t]);
+    max_leaf = std::max(max_leaf, leaf_of[(size_t)t]);
     total_nodes += tv.size;
     if (tv.size > max_nodes) max_nodes = tv.size;
     if (tv.dl)
@@ -321,10 +342,11 @@ ml2_status ml2_load_ensemble(const ml2_ensemble_desc *desc, ml2_ensemble **out) 
   f.num_features = d.num_features;
   f.base = d.base_score;
   f.ragged = ragged ? 1 : 0;
-  std::vector<char> host;
+  RaggedPack pk;
+  std::unique_ptr<char[]> perfect;
+  const char *host = nullptr;
   size_t bytes = 0;
   if (ragged) {
-    RaggedPack pk;
     try {
       pack_ragged(views, depths, &pk);
     } catch (const std::bad_alloc &) {
@@ -334,8 +356,8 @@ ml2_status ml2_load_ensemble(const ml2_ensemble_desc *desc, ml2_ensemble **out) 
     f.records = pk.slots;
     f.depth = pk.depth;
     f.rec_bytes = ml2::record_bytes(0);
-    host.swap(pk.bytes);
-    bytes = host.size();
+    host = pk.bytes.data();
+    bytes = pk.bytes.size();
   } else {
     f.num_trees_padded = (int32_t)tpad16;
     f.records = f.num_trees_padded;
@@ -343,16 +365,17 @@ ml2_status ml2_load_ensemble(const ml2_ensemble_desc *desc, ml2_ensemble **out) 
     f.rec_bytes = ml2::record_bytes(depth);
     bytes = (size_t)f.num_trees_padded * f.rec_bytes;
     try {
-      host.assign(bytes, 0);
+      perfect.reset(new char[bytes]);
+      host = perfect.get();
+      ml2::parallel_for(f.num_trees_padded, total_nodes, [&](int64_t t) {
+        char *rec = perfect.get() + (size_t)t * f.rec_bytes;
+        if (t < d.num_trees)
+          pad_tree(views[(size_t)t], depth, rec);
+        else
+          pad_identity_tree(depth, rec);
+      });
     } catch (const std::bad_alloc &) {
       return fail(ML2_ERR_OUT_OF_MEMORY, "host staging of %zu bytes failed", bytes);
-    }
-    for (int32_t t = 0; t < f.num_trees_padded; ++t) {
-      char *rec = host.data() + (size_t)t * f.rec_bytes;
-      if (t < d.num_trees)
-        pad_tree(views[(size_t)t], depth, rec);
-      else
-        pad_identity_tree(depth, rec);
     }
   }
   // The tree table is followed by kTreeSlack zero bytes: chunk staging reads
@@ -361,8 +384,8 @@ ml2_status ml2_load_ensemble(const ml2_ensemble_desc *desc, ml2_ensemble **out) 
   if (e == hipErrorOutOfMemory)
     return fail(ML2_ERR_OUT_OF_MEMORY, "hipMalloc(%zu)", bytes + ml2::kTreeSlack);
   if (e != hipSuccess) return hip_fail(e, "hipMalloc");
-  e = hipMemset(f.d_trees, 0, bytes + ml2::kTreeSlack);
-  if (e == hipSuccess) e = hipMemcpy(f.d_trees, host.data(), bytes, hipMemcpyHostToDevice);
+  e = hipMemset(static_cast<char *>(f.d_trees) + bytes, 0, ml2::kTreeSlack);
+  if (e == hipSuccess) e = hipMemcpy(f.d_trees, host, bytes, hipMemcpyHostToDevice);
   if (e != hipSuccess) {
     (void)hipFree(f.d_trees);
     return hip_fail(e, "hipMemcpy");

@@ -22,10 +22,9 @@ constexpr size_t kTreeSlack = 128 * 1024;  // readable zero bytes after the tree
 hipError_t ensure_dynamic_lds(const void *fn, size_t bytes);
 
 // The rank form of an ensemble of perfect trees (rank_pack.h) on the device;
-// ok = 0: the ensemble has none.
+// ok = 0: the ensemble has none, or ranking a row costs more than it saves.
 struct RankForm {
   int32_t ok, mode, depth, group, waves, per_cu;  // waves of a workgroup, workgroups of a CU
-  int32_t pays;  // the walk saves more than ranking a row costs
   int32_t nslots, nchunks, nlines;
   uint32_t slot_bytes, tile_bytes;
   void *block;  // one allocation holding every table below

@@ -50,37 +50,34 @@ void put_word(char *base, size_t cap, size_t at, uint32_t w) {
 void pad_tree(const TreeView &tv, int D, char *rec) {
   const uint32_t L = 1u << D;
   const size_t cap = record_bytes(D);
-  struct Item {
-    int32_t node;
-    uint32_t pos;  // heap position, 1-based
-  };
-  std::vector<Item> stack;
-  stack.push_back({0, 1u});
-  while (!stack.empty()) {
-    const Item it = stack.back();
-    stack.pop_back();
-    ML2_CHECK(it.node >= 0 && it.node < tv.size && it.pos >= 1 && it.pos < 2 * L);
-    const bool leaf = tv.left[it.node] == -1 && tv.right[it.node] == -1;
-    if (it.pos >= L) {  // only leaves reach depth D
-      ML2_CHECK(leaf);
-      put_word(rec, cap, 4u * L + 4u * it.pos, float_bits(tv.val[it.node]));  // byte 8L .. 12L
-      continue;
+  put_node(rec, cap, 0, 0u, 0u);
+  std::vector<int32_t> level(1, 0), below;  // node ids of a level, left to right
+  for (uint32_t pos0 = 1; pos0 < L; pos0 *= 2) {  // heap positions pos0 .. 2 pos0 - 1
+    below.resize(2 * (size_t)pos0);
+    for (uint32_t i = 0; i < pos0; ++i) {
+      const int32_t node = level[i];
+      ML2_CHECK(node >= 0 && node < tv.size);
+      const bool leaf = tv.left[node] == -1 && tv.right[node] == -1;
+      if (leaf)  // feature 0, threshold +0: both sides lead to the same value
+        put_node(rec, cap, 8u * (pos0 + i), 0u, 0u);
+      else
+        put_node(rec, cap, 8u * (pos0 + i), (uint32_t)tv.feat[node], float_bits(tv.thr[node]));
+      below[2 * i + 1] = leaf ? node : tv.left[node];  // taken iff x < threshold
+      below[2 * i] = leaf ? node : tv.right[node];
     }
-    if (leaf) {  // feature 0, threshold +0: both sides lead to the same value
-      put_node(rec, cap, 8u * it.pos, 0u, 0u);
-      stack.push_back({it.node, 2 * it.pos});
-      stack.push_back({it.node, 2 * it.pos + 1});
-    } else {
-      put_node(rec, cap, 8u * it.pos, (uint32_t)tv.feat[it.node], float_bits(tv.thr[it.node]));
-      stack.push_back({tv.left[it.node], 2 * it.pos + 1});  // taken iff x < threshold
-      stack.push_back({tv.right[it.node], 2 * it.pos});
-    }
+    level.swap(below);
+  }
+  if (cap > 12u * L) memset(rec + 12u * L, 0, cap - 12u * L);
+  for (uint32_t i = 0; i < L; ++i) {  // only leaves reach depth D
+    ML2_CHECK(tv.left[level[i]] == -1 && tv.right[level[i]] == -1);
+    put_word(rec, cap, 4u * L + 4u * (L + i), float_bits(tv.val[level[i]]));  // byte 8L .. 12L
   }
 }
 
 void pad_identity_tree(int D, char *rec) {
   const uint32_t L = 1u << D;
   const size_t cap = record_bytes(D);
+  memset(rec, 0, cap);
   for (uint32_t j = L; j < 2 * L; ++j) put_word(rec, cap, 4u * L + 4u * j, float_bits(-0.0f));
 }
 

@@ -22,8 +22,8 @@ struct TreeView {
   int64_t size;
 };
 
-// Fill the perfect-tree record of depth D (record_bytes(D) zeroed bytes at
-// rec) from a tree of depth <= D, replicating leaves that sit above depth D
+// Fill the perfect-tree record of depth D (record_bytes(D) bytes at rec) from
+// a tree of depth <= D, replicating leaves that sit above depth D
 // into dummy subtrees.
 void pad_tree(const TreeView &tv, int D, char *rec);
 

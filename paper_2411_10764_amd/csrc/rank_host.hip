@@ -83,12 +83,6 @@ void rank_load(const std::vector<TreeView> &views, Forest *f) {
     if (!rank_codes(views, f->num_features, &codes)) return;
     r.tile_bytes = codes.rows * kRankRow;
     if (!shape(r.tile_bytes, D, &r)) return;
-    RankPack p;
-    if (!rank_pack(views, codes, f->num_features, D, r.group, r.slot_bytes, &p)) return;
-    int64_t steps = 0, grids = 0;  // of ranking one row
-    for (const RankGroup &g : p.groups)
-      for (const RankSeg &sg : g.seg) steps += sg.put != kRankNone ? sg.steps : 0;
-    for (const RankGrid &g : p.grid) grids += g.top != 0.0f;
     // Ranking a row costs about 0.8 of a node visit per search step and one
     // per grid feature, and a visit of the rank walk takes about 0.3 of a
     // visit less than one of the float walk, so small ensembles over many
@@ -97,19 +91,25 @@ void rank_load(const std::vector<TreeView> &views, Forest *f) {
     // trees and wide rows leave those few trees per lane or few waves
     // (262,144 x 96, 100 trees of depth 10: 193 us against 101; 500,000 x
     // 256, 100 of depth 12: 47.3 ms against 1.3).
-    r.pays = D >= 9 || f->num_features > 128 ||
-             3 * (int64_t)f->num_trees * D >= 8 * steps + 10 * grids;
-    size_t bytes = 0;
-    const size_t o_slots = place(&bytes, p.data);
-    bytes += kTreeSlack;  // staging reads whole register sets past a slot
-    const size_t o_grid = place(&bytes, p.grid), o_lg = place(&bytes, p.line_group),
-                 o_gs = place(&bytes, p.group_slot), o_gr = place(&bytes, p.groups),
-                 o_ch = place(&bytes, p.chunks);
-    std::vector<char> host(bytes, 0);
+    int64_t steps = 0, grids = 0;  // of ranking one row
+    for (int32_t c = 0; c < f->num_features; ++c) {
+      for (size_t n = codes.table[(size_t)c].size(); n; n >>= 1) ++steps;
+      grids += codes.grid[(size_t)c].top != 0.0f;
+    }
+    if (D < 9 && f->num_features <= 128 &&
+        3 * (int64_t)f->num_trees * D < 8 * steps + 10 * grids)
+      return;
+    RankPack p;
+    if (!rank_pack(views, codes, f->num_features, D, r.group, r.slot_bytes, &p)) return;
+    size_t bytes = p.bytes + kTreeSlack;  // staging reads whole register sets past a slot
+    const size_t o_slots = 0, o_grid = place(&bytes, p.grid),
+                 o_lg = place(&bytes, p.line_group), o_gs = place(&bytes, p.group_slot),
+                 o_gr = place(&bytes, p.groups), o_ch = place(&bytes, p.chunks);
+    const size_t tail = p.bytes;  // zeros and the small tables
+    std::vector<char> host(bytes - tail, 0);
     auto put = [&](size_t o, const auto &v) {
-      if (!v.empty()) memcpy(host.data() + o, v.data(), v.size() * sizeof(v[0]));
+      if (!v.empty()) memcpy(host.data() + (o - tail), v.data(), v.size() * sizeof(v[0]));
     };
-    put(o_slots, p.data);
     put(o_grid, p.grid);
     put(o_lg, p.line_group);
     put(o_gs, p.group_slot);
@@ -119,7 +119,9 @@ void rank_load(const std::vector<TreeView> &views, Forest *f) {
       (void)hipGetLastError();  // the float walks need none of it
       return;
     }
-    if (hipMemcpy(r.block, host.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) {
+    if (hipMemcpy(r.block, p.data.get(), tail, hipMemcpyHostToDevice) != hipSuccess ||
+        hipMemcpy(static_cast<char *>(r.block) + tail, host.data(), host.size(),
+                  hipMemcpyHostToDevice) != hipSuccess) {
       (void)hipGetLastError();
       (void)hipFree(r.block);
       return;
@@ -157,7 +159,7 @@ void rank_free(Forest *f) {
 // 338 against 241).
 bool rank_takes(const Forest &f, int64_t n_work, int cu_count, bool perf) {
   const RankForm &r = f.rank;
-  if (!r.ok || !r.pays) return false;
+  if (!r.ok) return false;
   for (int t : {kTuneSplit, kTuneGroup, kTuneWaves, kTuneNbuf, kTuneChunk})
     if (get_tune(t) != 0) return false;  // the overrides shape the float walks
   return perf || n_work >= (int64_t)48 * r.waves * r.per_cu * cu_count;

@@ -1,10 +1,13 @@
 // Host side of the rank form (rank_pack.h).
 #include "rank_pack.h"
 
+#include "host_parallel.h"
+
 #include <math.h>
 #include <string.h>
 
 #include <algorithm>
+#include <memory>
 
 namespace ml2 {
 namespace {
@@ -165,6 +168,7 @@ int steps_of(size_t n) {
 // 1, padded with +inf.
 void put_search_tree(const float *t, size_t n, int s, char *dst) {
   const size_t size = (size_t)1 << s;
+  memset(dst, 0, 4);
   for (size_t u = 1; u < size; ++u) {
     const int l = steps_of(u) - 1;  // its level
     const size_t in_order = (((u - ((size_t)1 << l)) * 2 + 1) << (s - 1 - l)) - 1;
@@ -177,87 +181,104 @@ void put_search_tree(const float *t, size_t n, int s, char *dst) {
 void put_tree(const TreeView &tv, const RankCodes &codes, const uint16_t *code, int D,
               char *dst) {
   const int K = rank_top(D);
-  struct Item {
-    int32_t node;
-    int level;
-    uint32_t idx;
-  };
-  std::vector<Item> stack;
-  stack.push_back({0, 0, 0u});
-  while (!stack.empty()) {
-    const Item it = stack.back();
-    stack.pop_back();
-    const bool leaf = tv.left[it.node] == -1 && tv.right[it.node] == -1;
-    if (it.level == D) {
-      const uint32_t w = bits_of(tv.val[it.node]);
-      memcpy(dst + 4 * ((size_t)(1u << D) + it.idx), &w, 4);
-      continue;
+  memset(dst, 0, 4);
+  std::vector<int32_t> level(1, 0), below;  // node ids of a level, by idx
+  for (int l = 0; l < D; ++l) {
+    below.resize((size_t)2 << l);
+    for (uint32_t idx = 0; idx < 1u << l; ++idx) {
+      const int32_t node = level[idx];
+      const bool leaf = tv.left[node] == -1 && tv.right[node] == -1;
+      const uint32_t at =
+          l < K ? (idx << (K - l)) + (1u << (K - 1 - l)) : (1u << l) + idx;
+      // a replicated leaf: nothing is below 0, and both sides hold it
+      const uint32_t w = leaf ? 0u : node_word(codes, tv.feat[node], code[node]);
+      memcpy(dst + 4 * (size_t)at, &w, 4);
+      below[2 * idx + 1] = leaf ? node : tv.left[node];  // x < t
+      below[2 * idx] = leaf ? node : tv.right[node];
     }
-    const uint32_t at = it.level < K
-                            ? (it.idx << (K - it.level)) + (1u << (K - 1 - it.level))
-                            : (1u << it.level) + it.idx;
-    // a replicated leaf: nothing is below 0, and both sides hold it
-    const uint32_t w = leaf ? 0u : node_word(codes, tv.feat[it.node], code[it.node]);
-    memcpy(dst + 4 * (size_t)at, &w, 4);
-    const int32_t l = leaf ? it.node : tv.left[it.node], r = leaf ? it.node : tv.right[it.node];
-    stack.push_back({l, it.level + 1, 2 * it.idx + 1});
-    stack.push_back({r, it.level + 1, 2 * it.idx});
+    level.swap(below);
   }
+  for (uint32_t idx = 0; idx < 1u << D; ++idx)
+    memcpy(dst + 4 * ((size_t)(1u << D) + idx), &tv.val[level[idx]], 4);
 }
 
 }  // namespace
 
 bool rank_codes(const std::vector<TreeView> &views, int num_features, RankCodes *out) {
-  const size_t F = (size_t)num_features;
-  size_t nodes = 0;
-  std::vector<size_t> first(F + 1, 0);
-  for (const TreeView &tv : views) {
-    for (int64_t i = 0; i < tv.size; ++i)
-      if (tv.left[i] != -1) ++first[(size_t)tv.feat[i] + 1];
-    nodes += (size_t)tv.size;
-  }
+  const size_t F = (size_t)num_features, T = views.size();
+  std::vector<size_t> node0(T + 1, 0);  // first node of each tree
+  for (size_t t = 0; t < T; ++t) node0[t + 1] = node0[t] + (size_t)views[t].size;
+  const size_t nodes = node0[T];
   if (nodes > 0xFFFFFFFFull) return false;
-  for (size_t f = 0; f < F; ++f) first[f + 1] += first[f];
-  std::vector<Entry> all(first[F]), tmp(first[F]);
-  std::vector<size_t> at(first.begin(), first.end() - 1);
-  uint32_t base = 0;
-  for (const TreeView &tv : views) {
-    for (int64_t i = 0; i < tv.size; ++i)
-      if (tv.left[i] != -1)
-        all[at[(size_t)tv.feat[i]]++] = {key_of(tv.thr[i]), base + (uint32_t)i};
-    base += (uint32_t)tv.size;
+  // splits grouped by feature, in node order: counted and then placed by
+  // blocks of trees
+  const size_t blocks = std::min<size_t>(T, 16);
+  auto tree_of = [&](size_t b) { return T * b / blocks; };
+  std::vector<std::vector<size_t>> at(blocks, std::vector<size_t>(F, 0));
+  parallel_for((int64_t)blocks, (int64_t)nodes, [&](int64_t b) {
+    std::vector<size_t> &c = at[(size_t)b];
+    for (size_t t = tree_of((size_t)b); t < tree_of((size_t)b + 1); ++t)
+      for (int64_t i = 0; i < views[t].size; ++i)
+        if (views[t].left[i] != -1) ++c[(size_t)views[t].feat[i]];
+  });
+  std::vector<size_t> first(F + 1, 0);
+  for (size_t f = 0, sum = 0; f < F; ++f) {
+    first[f] = sum;
+    for (size_t b = 0; b < blocks; ++b) {
+      const size_t n = at[b][f];
+      at[b][f] = sum;
+      sum += n;
+    }
+    first[f + 1] = sum;
   }
-  out->code.assign(nodes, 0);
+  const size_t splits = first[F];
+  std::unique_ptr<Entry[]> all(new Entry[splits]), tmp(new Entry[splits]);
+  parallel_for((int64_t)blocks, (int64_t)nodes, [&](int64_t b) {
+    std::vector<size_t> &c = at[(size_t)b];
+    for (size_t t = tree_of((size_t)b); t < tree_of((size_t)b + 1); ++t) {
+      const TreeView &tv = views[t];
+      for (int64_t i = 0; i < tv.size; ++i)
+        if (tv.left[i] != -1)
+          all[c[(size_t)tv.feat[i]]++] = {key_of(tv.thr[i]), (uint32_t)(node0[t] + (size_t)i)};
+    }
+  });
+  out->code.reset(new uint16_t[nodes]);  // leaves' stay unset
   out->table.assign(F, {});
   out->grid.assign(F, RankGrid{0.0f, 0.0f, 0.0f, 0u});
   out->field.assign(F, RankField{0, 0, 0});
   std::vector<size_t> codes(F, 0);
-  for (size_t f = 0; f < F; ++f) {
-    const size_t n = first[f + 1] - first[f];
-    if (n == 0) continue;
-    Entry *e = all.data() + first[f];
-    sort_entries(e, tmp.data() + first[f], n);
+  std::vector<uint8_t> too_many(F, 0);
+  parallel_for((int64_t)F, (int64_t)nodes, [&](int64_t fi) {
+    const size_t f = (size_t)fi, n = first[f + 1] - first[f];
+    if (n == 0) return;
+    Entry *e = all.get() + first[f];
+    sort_entries(e, tmp.get() + first[f], n);
     std::vector<float> &t = out->table[f];
     for (size_t i = 0; i < n; ++i)
       if (i == 0 || e[i].key != e[i - 1].key) t.push_back(value_of(e[i].key));
-    if (t.size() > kMostThresholds) return false;
-    RankGrid g{};
+    const size_t n_t = t.size();
+    if (n_t > kMostThresholds) {
+      too_many[f] = 1;
+      return;
+    }
     // a grid whose codes take no wider a field than the table's would, or
     // that a byte holds (a table costs a search)
-    const size_t n_t = t.size();
+    RankGrid g{};
     const bool grid = find_grid(t, n_t <= 255 ? 255 : n_t <= 4095 ? 4095 : 65535, &g);
-    size_t j = 0;
-    for (size_t i = 0; i < n; ++i) {
-      if (i && e[i].key != e[i - 1].key) ++j;
-      out->code[e[i].node] =
-          (uint16_t)(grid ? (int64_t)((double)t[j] * g.scale + g.bias) : (int64_t)j + 1);
+    uint32_t c = 0;
+    for (size_t i = 0, j = 0; i < n; ++i) {
+      if (i == 0 || e[i].key != e[i - 1].key)
+        c = grid ? (uint32_t)((double)t[j++] * g.scale + g.bias) : (uint32_t)++j;
+      out->code[e[i].node] = (uint16_t)c;
     }
-    codes[f] = grid ? (size_t)g.top : t.size();
+    codes[f] = grid ? (size_t)g.top : n_t;
     if (grid) {
       out->grid[f] = g;
       t.clear();
     }
-  }
+  });
+  for (uint8_t m : too_many)
+    if (m) return false;
   place_fields(codes, out);
   return true;
 }
@@ -272,12 +293,17 @@ bool rank_pack(const std::vector<TreeView> &views, const RankCodes &codes, int n
   out->lines = (num_features + kRankLine - 1) / kRankLine;
   out->grid.assign((size_t)out->lines * kRankLine, RankGrid{0.0f, 0.0f, 0.0f, 0u});
   uint32_t fill = 0;  // bytes used of the last slot
-  auto slot = [&](int s) { return out->data.data() + (size_t)s * slot_bytes; };
   auto new_slot = [&]() {
-    out->data.resize(out->data.size() + slot_bytes, 0);
     ++out->slots;
     fill = 0;
   };
+  struct Table {  // a search tree to write once the slots are laid out
+    const float *t;
+    size_t n;
+    int steps, slot;
+    uint32_t offset;
+  };
+  std::vector<Table> tables;
   new_slot();
   // the order in which the kernels write codes, and so which of a dword's
   // fields comes first: per line the grid features, then the groups
@@ -335,7 +361,7 @@ bool rank_pack(const std::vector<TreeView> &views, const RankCodes &codes, int n
           out->groups.back().seg[i].put = kRankNone;
         }
         ++in_group;
-        put_search_tree(t.data() + done, n, steps, slot(out->slots - 1) + fill);
+        tables.push_back({t.data() + done, n, steps, out->slots - 1, fill});
         fill += 4u << steps;
         done += n;
         if (done < t.size()) {  // the rest in a slot and a group of its own
@@ -347,9 +373,8 @@ bool rank_pack(const std::vector<TreeView> &views, const RankCodes &codes, int n
   }
   out->line_group.push_back((int32_t)out->groups.size());
   fill = (fill + 127u) & ~127u;  // trees start on a bank row
-  size_t node0 = 0, t = 0;
   const size_t total = (views.size() + group - 1) / group * group;
-  while (t < total) {
+  for (size_t t = 0; t < total;) {
     uint32_t fit = fill < slot_bytes ? (slot_bytes - fill) / RB / group * group : 0;
     if (fit == 0) {
       new_slot();
@@ -357,17 +382,33 @@ bool rank_pack(const std::vector<TreeView> &views, const RankCodes &codes, int n
     }
     const size_t n = std::min<size_t>(fit, total - t);
     out->chunks.push_back({out->slots - 1, (int32_t)fill, (int32_t)n, 0});
-    for (size_t i = 0; i < n; ++i, ++t, fill += RB) {
-      char *dst = slot(out->slots - 1) + fill;
+    fill += (uint32_t)n * RB;
+    t += n;
+  }
+  out->bytes = (size_t)out->slots * slot_bytes;
+  out->data.reset(new char[out->bytes]);  // bytes between tables and trees stay unset, unread
+  auto slot = [&](int s) { return out->data.get() + (size_t)s * slot_bytes; };
+  parallel_for((int64_t)tables.size(), (int64_t)tables.size() * 512, [&](int64_t i) {
+    const Table &t = tables[(size_t)i];
+    put_search_tree(t.t, t.n, t.steps, slot(t.slot) + t.offset);
+  });
+  std::vector<size_t> node0(views.size() + 1, 0), first(out->chunks.size() + 1, 0);
+  for (size_t t = 0; t < views.size(); ++t) node0[t + 1] = node0[t] + (size_t)views[t].size;
+  for (size_t c = 0; c < out->chunks.size(); ++c)
+    first[c + 1] = first[c] + (size_t)out->chunks[c].trees;
+  parallel_for((int64_t)out->chunks.size(), (int64_t)node0.back(), [&](int64_t c) {
+    const RankChunk &ch = out->chunks[(size_t)c];
+    char *dst = slot(ch.slot) + ch.offset;
+    for (size_t t = first[(size_t)c]; t < first[(size_t)c + 1]; ++t, dst += RB) {
       if (t < views.size()) {
-        put_tree(views[t], codes, codes.code.data() + node0, D, dst);
-        node0 += (size_t)views[t].size;
+        put_tree(views[t], codes, codes.code.get() + node0[t], D, dst);
       } else {  // padding: every leaf -0.0 (x + (-0.0) == x)
         const uint32_t z = 0x80000000u;
+        memset(dst, 0, (size_t)4 << D);
         for (uint32_t j = 1u << D; j < 2u << D; ++j) memcpy(dst + 4 * (size_t)j, &z, 4);
       }
     }
-  }
+  });
   return true;
 }
 

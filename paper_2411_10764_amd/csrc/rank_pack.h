@@ -41,6 +41,7 @@
 
 #include <stdint.h>
 
+#include <memory>
 #include <vector>
 
 #include "pack.h"
@@ -90,7 +91,8 @@ struct RankPack {
   RankMode mode = kRankByte;
   int lines = 0, slots = 0, group = 0;
   uint32_t rows = 0;                   // dword rows of the tile
-  std::vector<char> data;              // slots * slot_bytes
+  size_t bytes = 0;                    // slots * slot_bytes
+  std::unique_ptr<char[]> data;
   std::vector<RankGrid> grid;          // lines * kRankLine
   std::vector<int32_t> line_group;     // lines + 1: first group of each line
   std::vector<int32_t> group_slot;
@@ -111,7 +113,7 @@ struct RankCodes {
   std::vector<RankField> field;           // per feature
   std::vector<std::vector<float>> table;  // per feature; empty for grid features
   std::vector<RankGrid> grid;             // per feature
-  std::vector<uint16_t> code;             // per node, trees in order
+  std::unique_ptr<uint16_t[]> code;       // per node, trees in order
 };
 bool rank_codes(const std::vector<TreeView> &views, int num_features, RankCodes *out);
 

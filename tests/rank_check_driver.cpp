@@ -114,7 +114,7 @@ static void check(int D, int F, int trees, int group, uint32_t slot_bytes, bool 
   CHECK(rank_pack(views, codes, F, D, group, slot_bytes, &p));
   const uint32_t RB = rank_tree_bytes(D), tile = p.rows * kRankRow;
   const int K = rank_top(D);
-  CHECK(p.data.size() == (size_t)p.slots * slot_bytes);
+  CHECK(p.bytes == (size_t)p.slots * slot_bytes);
   CHECK((int)p.line_group.size() == p.lines + 1 && p.grid.size() == (size_t)p.lines * kRankLine);
   const uint32_t buf = tile + 1024;  // LDS address of the slot, beyond the tile
   std::vector<float> x((size_t)F);
@@ -162,7 +162,7 @@ static void check(int D, int F, int trees, int group, uint32_t slot_bytes, bool 
           const uint32_t steps = p.groups[(size_t)g].seg[0].steps;
           CHECK(s.steps == steps && steps > 0 && s.table_off % 4 == 0);
           CHECK(s.table_off + (4u << steps) <= slot_bytes);
-          const char *tab = p.data.data() + (size_t)at_slot * slot_bytes + s.table_off;
+          const char *tab = p.data.get() + (size_t)at_slot * slot_bytes + s.table_off;
           const float v = x[(size_t)(l * kRankLine + (int)s.lane_reg)];
           const uint32_t first = buf + s.table_off;
           float a = as_float(first + 4);
@@ -188,7 +188,7 @@ static void check(int D, int F, int trees, int group, uint32_t slot_bytes, bool 
         auto word = [&](uint32_t at) {
           CHECK(at >= rec + 4 && at + 4 <= rec + RB && at % 4 == 0);
           uint32_t w;
-          memcpy(&w, p.data.data() + (size_t)at_slot * slot_bytes + (at - buf), 4);
+          memcpy(&w, p.data.get() + (size_t)at_slot * slot_bytes + (at - buf), 4);
           return w;
         };
         float a = as_float(rec);
