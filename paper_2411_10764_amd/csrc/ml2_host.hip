@@ -390,7 +390,7 @@ ml2_status ml2_load_ensemble(const ml2_ensemble_desc *desc, ml2_ensemble **out) 
     (void)hipFree(f.d_trees);
     return hip_fail(e, "hipMemcpy");
   }
-  ml2::rank_load(views, &f);
+  ml2::rank_load(views, ragged ? &pk : nullptr, &f);
   ml2_ensemble *h = new (std::nothrow) ml2_ensemble;
   if (!h) {
     ml2::rank_free(&f);

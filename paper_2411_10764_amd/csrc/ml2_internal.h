@@ -21,7 +21,7 @@ constexpr size_t kTreeSlack = 128 * 1024;  // readable zero bytes after the tree
 // once per kernel, device and size increase).
 hipError_t ensure_dynamic_lds(const void *fn, size_t bytes);
 
-// The rank form of an ensemble of perfect trees (rank_pack.h) on the device;
+// The rank form of an ensemble (rank_pack.h) on the device;
 // ok = 0: the ensemble has none, or ranking a row costs more than it saves.
 struct RankForm {
   int32_t ok, mode, depth, group, waves, per_cu;  // waves of a workgroup, workgroups of a CU
@@ -42,7 +42,7 @@ struct Forest {
   float base;
   uint32_t rec_bytes;       // record_bytes(depth), or record_bytes(0) when ragged
   void *d_trees;            // records * rec_bytes bytes (+ kTreeSlack zero bytes)
-  RankForm rank;            // perfect trees only
+  RankForm rank;
 };
 
 // Launch parameters of a walk (chosen on the host from D and F).
@@ -73,11 +73,12 @@ hipError_t launch_fused(const Forest &v, const Forest &p, const WalkPlan &pl, in
                         const float *X, int64_t n, int64_t ld, uint8_t *valid_out,
                         float *margin_out, float *score_out, hipStream_t s);
 
-// Builds the rank form of `f` (perfect trees of `views`, F features) on the
-// current device; without one (too many thresholds, no fitting slot, no
+// Builds the rank form of `f` (perfect trees of `views`, or the ragged slots
+// they were packed into) on the current device; without one (too many thresholds, no fitting slot, no
 // memory) f->rank.ok stays 0 and the float walks take every call.
 struct TreeView;
-void rank_load(const std::vector<TreeView> &views, Forest *f);
+struct RaggedPack;
+void rank_load(const std::vector<TreeView> &views, const RaggedPack *ragged, Forest *f);
 void rank_free(Forest *f);
 // Whether a walk of n_work rows (perf: the performance walk) takes the rank form.
 bool rank_takes(const Forest &f, int64_t n_work, int cu_count, bool perf);

@@ -13,7 +13,7 @@ namespace {
 constexpr uint32_t kMaxSlot = 64 * 1024;
 
 // The register class of a kernel that shares a CU with `total` waves in all.
-int wave_class(int total) { return total > 12 ? 16 : total > 8 ? 12 : total > 4 ? 8 : 4; }
+int wave_class(int total) { return total > 16 ? 24 : total > 12 ? 16 : total > 8 ? 12 : total > 4 ? 8 : 4; }
 
 // Bytes that the staging registers of `waves` waves of a class hold.
 size_t stage_bytes(int cls, int waves) {
@@ -64,6 +64,40 @@ bool shape(uint32_t tile, int D, RankForm *r) {
   return false;
 }
 
+// The same for ragged trees, whose slot is fixed.  The walk is bound by the
+// latency of its chain of reads, so as many waves as fit, two workgroups of
+// twelve first (16M x 128 round, 300 trees of depth up to 14 over 64
+// features: 8 waves per CU 9.2 ms, 12 6.6, 16 5.4, 24 4.6).
+size_t ragged_lds(uint32_t tile, int waves) {
+  // a leaf reads a code within ragged_mask of its lane's column
+  size_t past = kRankRow;
+  while (past < tile) past *= 2;
+  const size_t fixed = kRaggedChunkBytes + (size_t)waves * tile;
+  return std::max(fixed + queue_bytes(waves) + waves * sizeof(int), fixed - tile + kRankRow + past);
+}
+
+uint32_t ragged_mask(uint32_t tile, RankMode mode) {
+  uint32_t past = kRankRow;
+  while (past < tile) past *= 2;
+  return (past - 1) & (mode == kRankByte ? ~0xFCu : ~0xFDu);
+}
+
+bool ragged_shape(uint32_t tile, RankForm *r) {
+  struct Shape {
+    int waves, per_cu;
+  };
+  const Shape shapes[] = {{12, 2}, {16, 1}, {12, 1}, {8, 1}, {4, 1}};  // (four hold any tile)
+  for (const Shape &sh : shapes) {
+    if (ragged_lds(tile, sh.waves) * sh.per_cu > kLdsBudget) continue;
+    r->waves = sh.waves;
+    r->per_cu = sh.per_cu;
+    r->group = 1;
+    r->slot_bytes = kRaggedChunkBytes;
+    return true;
+  }
+  return false;
+}
+
 template <typename T>
 size_t place(size_t *at, const std::vector<T> &v) {
   const size_t o = *at;
@@ -73,16 +107,17 @@ size_t place(size_t *at, const std::vector<T> &v) {
 
 }  // namespace
 
-void rank_load(const std::vector<TreeView> &views, Forest *f) {
+void rank_load(const std::vector<TreeView> &views, const RaggedPack *ragged, Forest *f) {
   RankForm r{};
   f->rank = r;
   const int D = f->depth;
-  if (f->ragged || D < kRankMinDepth || D > kRankMaxDepth) return;
+  if (!ragged && (D < kRankMinDepth || D > kRankMaxDepth)) return;
   try {
     RankCodes codes;
     if (!rank_codes(views, f->num_features, &codes)) return;
+    if (ragged && !rank_ragged_fields(&codes)) return;
     r.tile_bytes = codes.rows * kRankRow;
-    if (!shape(r.tile_bytes, D, &r)) return;
+    if (!(ragged ? ragged_shape(r.tile_bytes, &r) : shape(r.tile_bytes, D, &r))) return;
     // Ranking a row costs about 0.8 of a node visit per search step and one
     // per grid feature, and a visit of the rank walk takes about 0.3 of a
     // visit less than one of the float walk, so small ensembles over many
@@ -90,17 +125,19 @@ void rank_load(const std::vector<TreeView> &views, Forest *f) {
     // us against 58; 16M x 128, 300 of depth 6: 7.84 ms against 7.0).  Deep
     // trees and wide rows leave those few trees per lane or few waves
     // (262,144 x 96, 100 trees of depth 10: 193 us against 101; 500,000 x
-    // 256, 100 of depth 12: 47.3 ms against 1.3).
+    // 256, 100 of depth 12: 47.3 ms against 1.3).  A ragged tree's walk saves
+    // about nine such visits.
     int64_t steps = 0, grids = 0;  // of ranking one row
     for (int32_t c = 0; c < f->num_features; ++c) {
       for (size_t n = codes.table[(size_t)c].size(); n; n >>= 1) ++steps;
       grids += codes.grid[(size_t)c].top != 0.0f;
     }
-    if (D < 9 && f->num_features <= 128 &&
-        3 * (int64_t)f->num_trees * D < 8 * steps + 10 * grids)
-      return;
+    const int64_t saves = ragged ? 90 * (int64_t)f->num_trees : 3 * (int64_t)f->num_trees * D;
+    if ((ragged || (D < 9 && f->num_features <= 128)) && saves < 8 * steps + 10 * grids) return;
     RankPack p;
-    if (!rank_pack(views, codes, f->num_features, D, r.group, r.slot_bytes, &p)) return;
+    if (!(ragged ? rank_pack_ragged(*ragged, codes, f->num_features, &p)
+                 : rank_pack(views, codes, f->num_features, D, r.group, r.slot_bytes, &p)))
+      return;
     size_t bytes = p.bytes + kTreeSlack;  // staging reads whole register sets past a slot
     const size_t o_slots = 0, o_grid = place(&bytes, p.grid),
                  o_lg = place(&bytes, p.line_group), o_gs = place(&bytes, p.group_slot),
@@ -204,7 +241,10 @@ RankArgs args_for(const Forest &f, const float *X, int64_t n, int64_t ld, int cu
                ? 1
                : 0;
   a.base = f.base;
-  l->lds = (size_t)w * r.tile_bytes + r.slot_bytes + (perf ? queue_bytes(w) : 0);
+  a.missing = r.mode == kRankByte ? kRankRaggedByte : kRankRaggedHalf;
+  a.off_mask = ragged_mask(r.tile_bytes, (RankMode)r.mode);
+  l->lds = f.ragged ? ragged_lds(r.tile_bytes, w)
+                    : (size_t)w * r.tile_bytes + r.slot_bytes + (perf ? queue_bytes(w) : 0);
   l->cls = wave_class(w * per_cu);
   l->grid = (int)std::max<int64_t>(1, std::min<int64_t>(units, (int64_t)cu_count * per_cu));
   return a;
@@ -212,13 +252,23 @@ RankArgs args_for(const Forest &f, const float *X, int64_t n, int64_t ld, int cu
 
 }  // namespace
 
+// A slot must fit the staging registers of the launch, or its end would stay
+// unwritten.
+static bool stages_slot(const Forest &f, const RankArgs &a, const Launch &l) {
+  const int regs = f.ragged ? rank_ragged_stage_regs(l.cls) : rank_stage_regs(l.cls);
+  return (size_t)regs * 16 * a.nthreads >= a.slot_bytes && l.lds <= kLdsBudget;
+}
+
 hipError_t launch_rank_validity(const Forest &f, const float *X, int64_t n, int64_t ld,
                                 uint8_t *valid_out, float *margin_out, int cu_count,
                                 hipStream_t s) {
   Launch l{};
   RankArgs a = args_for(f, X, n, ld, cu_count, false, &l);
+  if (!stages_slot(f, a, l)) return hipErrorInvalidValue;
   a.valid_out = valid_out;
   a.margin_out = margin_out;
+  if (f.ragged)
+    return launch_rank_ragged_kernel(false, (RankMode)f.rank.mode, l.cls, a, l.grid, l.lds, s);
   return launch_rank_validity_kernel(f.rank.depth, (RankMode)f.rank.mode, f.rank.group,
                                      l.cls, a, l.grid, l.lds, s);
 }
@@ -228,8 +278,11 @@ hipError_t launch_rank_perf(const Forest &f, const float *X, int64_t n, int64_t 
                             hipStream_t s) {
   Launch l{};
   RankArgs a = args_for(f, X, n, ld, cu_count, true, &l);
+  if (!stages_slot(f, a, l)) return hipErrorInvalidValue;
   a.valid_in = valid;
   a.score_out = score_out;
+  if (f.ragged)
+    return launch_rank_ragged_kernel(true, (RankMode)f.rank.mode, l.cls, a, l.grid, l.lds, s);
   return launch_rank_perf_kernel(f.rank.depth, (RankMode)f.rank.mode, f.rank.group,
                                  l.cls, a, l.grid, l.lds, s);
 }

@@ -42,14 +42,11 @@ struct Entry {
 // included, fits 16 bits.
 constexpr size_t kMostThresholds = 65535 - 8192;
 
-// Stable LSD radix sort by key (11-bit digits); short lists by comparison.
-void sort_entries(Entry *e, Entry *tmp, size_t n) {
-  if (n < 2048) {
-    std::sort(e, e + n, [](const Entry &a, const Entry &b) { return a.key < b.key; });
-    return;
-  }
-  constexpr int B = 11;
-  for (int pass = 0; pass < 3; ++pass) {
+// Stable LSD radix sort by key in `passes` digits of B bits; the result is in
+// e (passes even) or tmp.
+template <int B>
+void radix_passes(Entry *e, Entry *tmp, size_t n, int passes) {
+  for (int pass = 0; pass < passes; ++pass) {
     uint32_t count[1 << B] = {0};
     const int sh = pass * B;
     for (size_t i = 0; i < n; ++i) ++count[(e[i].key >> sh) & ((1u << B) - 1)];
@@ -62,7 +59,20 @@ void sort_entries(Entry *e, Entry *tmp, size_t n) {
     for (size_t i = 0; i < n; ++i) tmp[count[(e[i].key >> sh) & ((1u << B) - 1)]++] = e[i];
     std::swap(e, tmp);
   }
-  memcpy(tmp, e, n * sizeof(Entry));  // three passes end in the other buffer
+}
+
+// By key, ascending: comparisons for a few entries, else radix digits small
+// enough for their counters not to cost more than the entries (1,000 entries:
+// 40 us by comparisons, 8 us by bytes).
+void sort_entries(Entry *e, Entry *tmp, size_t n) {
+  if (n < 64) {
+    std::sort(e, e + n, [](const Entry &a, const Entry &b) { return a.key < b.key; });
+  } else if (n < 8192) {
+    radix_passes<8>(e, tmp, n, 4);
+  } else {
+    radix_passes<11>(e, tmp, n, 3);
+    memcpy(e, tmp, n * sizeof(Entry));
+  }
 }
 
 // The grid of a sorted list of distinct thresholds: multiples of a power of
@@ -202,6 +212,106 @@ void put_tree(const TreeView &tv, const RankCodes &codes, const uint16_t *code, 
     memcpy(dst + 4 * ((size_t)(1u << D) + idx), &tv.val[level[idx]], 4);
 }
 
+struct Table {  // a search tree to write once the slots are laid out
+  const float *t;
+  size_t n;
+  int steps, slot;
+  uint32_t offset;
+};
+
+// Grids, table segments and their groups in slots of slot_bytes, from slot 0
+// on, each from byte `base` on; *fill: the bytes used of the last slot.
+void lay_out_tables(const RankCodes &codes, int num_features, uint32_t slot_bytes, uint32_t base,
+                    RankPack *out, std::vector<Table> *tables, uint32_t *fill) {
+  auto new_slot = [&]() {
+    ++out->slots;
+    *fill = base;
+  };
+  new_slot();
+  out->mode = codes.mode;
+  out->rows = codes.rows;
+  out->lines = (num_features + kRankLine - 1) / kRankLine;
+  out->grid.assign((size_t)out->lines * kRankLine, RankGrid{0.0f, 0.0f, 0.0f, 0u});
+  // the order in which the kernels write codes, and so which of a dword's
+  // fields comes first: per line the grid features, then the groups
+  std::vector<uint8_t> written(codes.rows, 0);
+  auto put_of = [&](int f, bool again) {
+    const RankField &fd = codes.field[(size_t)f];
+    const uint32_t dword = fd.off & ~3u, bit = (fd.off & 3u) * 8u + fd.low;
+    uint8_t &w = written[dword / kRankRow];
+    const uint32_t put = dword | (bit << 16) | ((w || again) ? kRankAdd : 0u);
+    w = 1;
+    return put;
+  };
+  for (int l = 0; l < out->lines; ++l) {
+    out->line_group.push_back((int32_t)out->groups.size());
+    std::vector<int> search;
+    for (int f = l * kRankLine; f < std::min(num_features, (l + 1) * kRankLine); ++f) {
+      if (codes.grid[(size_t)f].top != 0.0f) {
+        out->grid[(size_t)f] = codes.grid[(size_t)f];
+        out->grid[(size_t)f].put = put_of(f, false);
+      } else if (!codes.table[(size_t)f].empty()) {
+        search.push_back(f);
+      }
+    }
+    // tables of like sizes next to one another, so that they share groups
+    std::stable_sort(search.begin(), search.end(), [&](int a, int b) {
+      return codes.table[(size_t)a].size() < codes.table[(size_t)b].size();
+    });
+    int in_group = 4, group_steps = 0;  // segments of the open group (4: none open)
+    for (int f : search) {
+      const std::vector<float> &t = codes.table[(size_t)f];
+      for (size_t done = 0; done < t.size();) {
+        size_t n = t.size() - done;
+        int steps = steps_of(n);
+        if (*fill + (4u << steps) > slot_bytes) {
+          if (*fill != base) {
+            new_slot();
+            in_group = 4;
+          }
+          while ((4u << steps) > slot_bytes || steps > 13) --steps;
+          n = std::min(n, ((size_t)1 << steps) - 1);
+        }
+        if (in_group == 4 || group_steps != steps) {
+          out->groups.push_back(RankGroup{});
+          out->group_slot.push_back(out->slots - 1);
+          in_group = 0;
+          group_steps = steps;
+        }
+        RankSeg &s = out->groups.back().seg[in_group];
+        s.lane_reg = (uint32_t)(f % kRankLine) | ((uint32_t)n << 8);
+        s.put = put_of(f, done != 0);
+        s.table_off = *fill;
+        s.steps = (uint32_t)steps;
+        for (int i = in_group + 1; i < 4; ++i) {  // repeats until another segment takes the place
+          out->groups.back().seg[i] = s;
+          out->groups.back().seg[i].put = kRankNone;
+        }
+        ++in_group;
+        tables->push_back({t.data() + done, n, steps, out->slots - 1, *fill});
+        *fill += 4u << steps;
+        done += n;
+        if (done < t.size()) {  // the rest in a slot and a group of its own
+          new_slot();
+          in_group = 4;
+        }
+      }
+    }
+  }
+  out->line_group.push_back((int32_t)out->groups.size());
+}
+
+// Room for the slots, and the tables in them.
+void put_tables(const std::vector<Table> &tables, uint32_t slot_bytes, RankPack *out) {
+  out->bytes = (size_t)out->slots * slot_bytes;
+  out->data.reset(new char[out->bytes]);  // bytes between tables and trees stay unset, unread
+  parallel_for((int64_t)tables.size(), (int64_t)tables.size() * 512, [&](int64_t i) {
+    const Table &t = tables[(size_t)i];
+    put_search_tree(t.t, t.n, t.steps,
+                    out->data.get() + (size_t)t.slot * slot_bytes + t.offset);
+  });
+}
+
 }  // namespace
 
 bool rank_codes(const std::vector<TreeView> &views, int num_features, RankCodes *out) {
@@ -287,97 +397,17 @@ bool rank_pack(const std::vector<TreeView> &views, const RankCodes &codes, int n
                int D, int group, uint32_t slot_bytes, RankPack *out) {
   const uint32_t RB = rank_tree_bytes(D);
   if (slot_bytes % 16 || (uint64_t)group * RB > slot_bytes) return false;
-  out->mode = codes.mode;
-  out->rows = codes.rows;
   out->group = group;
-  out->lines = (num_features + kRankLine - 1) / kRankLine;
-  out->grid.assign((size_t)out->lines * kRankLine, RankGrid{0.0f, 0.0f, 0.0f, 0u});
   uint32_t fill = 0;  // bytes used of the last slot
-  auto new_slot = [&]() {
-    ++out->slots;
-    fill = 0;
-  };
-  struct Table {  // a search tree to write once the slots are laid out
-    const float *t;
-    size_t n;
-    int steps, slot;
-    uint32_t offset;
-  };
   std::vector<Table> tables;
-  new_slot();
-  // the order in which the kernels write codes, and so which of a dword's
-  // fields comes first: per line the grid features, then the groups
-  std::vector<uint8_t> written(codes.rows, 0);
-  auto put_of = [&](int f, bool again) {
-    const RankField &fd = codes.field[(size_t)f];
-    const uint32_t dword = fd.off & ~3u, bit = (fd.off & 3u) * 8u + fd.low;
-    uint8_t &w = written[dword / kRankRow];
-    const uint32_t put = dword | (bit << 16) | ((w || again) ? kRankAdd : 0u);
-    w = 1;
-    return put;
-  };
-  for (int l = 0; l < out->lines; ++l) {
-    out->line_group.push_back((int32_t)out->groups.size());
-    std::vector<int> search;
-    for (int f = l * kRankLine; f < std::min(num_features, (l + 1) * kRankLine); ++f) {
-      if (codes.grid[(size_t)f].top != 0.0f) {
-        out->grid[(size_t)f] = codes.grid[(size_t)f];
-        out->grid[(size_t)f].put = put_of(f, false);
-      } else if (!codes.table[(size_t)f].empty()) {
-        search.push_back(f);
-      }
-    }
-    // tables of like sizes next to one another, so that they share groups
-    std::stable_sort(search.begin(), search.end(), [&](int a, int b) {
-      return codes.table[(size_t)a].size() < codes.table[(size_t)b].size();
-    });
-    int in_group = 4, group_steps = 0;  // segments of the open group (4: none open)
-    for (int f : search) {
-      const std::vector<float> &t = codes.table[(size_t)f];
-      for (size_t done = 0; done < t.size();) {
-        size_t n = t.size() - done;
-        int steps = steps_of(n);
-        if (fill + (4u << steps) > slot_bytes) {
-          if (fill != 0) {
-            new_slot();
-            in_group = 4;
-          }
-          while ((4u << steps) > slot_bytes || steps > 13) --steps;
-          n = std::min(n, ((size_t)1 << steps) - 1);
-        }
-        if (in_group == 4 || group_steps != steps) {
-          out->groups.push_back(RankGroup{});
-          out->group_slot.push_back(out->slots - 1);
-          in_group = 0;
-          group_steps = steps;
-        }
-        RankSeg &s = out->groups.back().seg[in_group];
-        s.lane_reg = (uint32_t)(f % kRankLine);
-        s.put = put_of(f, done != 0);
-        s.table_off = fill;
-        s.steps = (uint32_t)steps;
-        for (int i = in_group + 1; i < 4; ++i) {  // repeats until another segment takes the place
-          out->groups.back().seg[i] = s;
-          out->groups.back().seg[i].put = kRankNone;
-        }
-        ++in_group;
-        tables.push_back({t.data() + done, n, steps, out->slots - 1, fill});
-        fill += 4u << steps;
-        done += n;
-        if (done < t.size()) {  // the rest in a slot and a group of its own
-          new_slot();
-          in_group = 4;
-        }
-      }
-    }
-  }
-  out->line_group.push_back((int32_t)out->groups.size());
+  lay_out_tables(codes, num_features, slot_bytes, 0, out, &tables, &fill);
   fill = (fill + 127u) & ~127u;  // trees start on a bank row
   const size_t total = (views.size() + group - 1) / group * group;
   for (size_t t = 0; t < total;) {
     uint32_t fit = fill < slot_bytes ? (slot_bytes - fill) / RB / group * group : 0;
     if (fit == 0) {
-      new_slot();
+      ++out->slots;
+      fill = 0;
       fit = slot_bytes / RB / group * group;
     }
     const size_t n = std::min<size_t>(fit, total - t);
@@ -385,13 +415,8 @@ bool rank_pack(const std::vector<TreeView> &views, const RankCodes &codes, int n
     fill += (uint32_t)n * RB;
     t += n;
   }
-  out->bytes = (size_t)out->slots * slot_bytes;
-  out->data.reset(new char[out->bytes]);  // bytes between tables and trees stay unset, unread
+  put_tables(tables, slot_bytes, out);
   auto slot = [&](int s) { return out->data.get() + (size_t)s * slot_bytes; };
-  parallel_for((int64_t)tables.size(), (int64_t)tables.size() * 512, [&](int64_t i) {
-    const Table &t = tables[(size_t)i];
-    put_search_tree(t.t, t.n, t.steps, slot(t.slot) + t.offset);
-  });
   std::vector<size_t> node0(views.size() + 1, 0), first(out->chunks.size() + 1, 0);
   for (size_t t = 0; t < views.size(); ++t) node0[t + 1] = node0[t] + (size_t)views[t].size;
   for (size_t c = 0; c < out->chunks.size(); ++c)
@@ -409,6 +434,73 @@ bool rank_pack(const std::vector<TreeView> &views, const RankCodes &codes, int n
       }
     }
   });
+  return true;
+}
+
+bool rank_ragged_fields(RankCodes *codes) {
+  std::vector<size_t> n(codes->field.size(), 0);
+  size_t most = 0;
+  for (size_t f = 0; f < n.size(); ++f) {
+    n[f] = codes->grid[f].top != 0.0f ? (size_t)codes->grid[f].top : codes->table[f].size();
+    most = std::max(most, n[f]);
+  }
+  if (most > 4095) return false;  // (a table then fits a slot)
+  codes->mode = most < (size_t)kRankRaggedByte ? kRankByte : kRankHalf;
+  uint32_t used = 0;
+  const uint32_t per = codes->mode == kRankByte ? 4 : 2;  // codes per dword
+  for (size_t f = 0; f < n.size(); ++f) {
+    codes->field[f] = RankField{0, 0, 0};
+    if (n[f] == 0) continue;
+    codes->field[f] = codes->mode == kRankByte
+                          ? RankField{used / 4 * kRankRow + used % 4, 0, 8}
+                          : RankField{used / 2 * kRankRow + used % 2 * 2, 3, 13};
+    ++used;
+  }
+  codes->rows = std::max<uint32_t>(1, (used + per - 1) / per);
+  return true;
+}
+
+bool rank_pack_ragged(const RaggedPack &ragged, const RankCodes &codes, int num_features,
+                      RankPack *out) {
+  constexpr uint32_t SB = kRaggedChunkBytes;
+  uint32_t fill = 0;
+  std::vector<Table> tables;
+  // (the slot lies at LDS address 0, and a search subtracts 4 from its table's)
+  lay_out_tables(codes, num_features, SB, 16, out, &tables, &fill);
+  const int slot0 = fill != 16 ? out->slots : 0;  // the first slot of trees
+  out->slots = slot0 + ragged.slots;
+  put_tables(tables, SB, out);
+  char *dst0 = out->data.get() + (size_t)slot0 * SB;
+  memcpy(dst0, ragged.bytes.data(), (size_t)ragged.slots * SB);
+  const uint32_t unit = codes.mode == kRankByte ? 256u : 8u;
+  for (int s = 0; s < ragged.slots; ++s) {
+    char *slot = dst0 + (size_t)s * SB;
+    uint32_t head[4];  // trees, deepest path, the sentinel's node, first tree
+    memcpy(head, slot, sizeof head);
+    out->chunks.push_back({slot0 + s, 0, (int32_t)head[0], 0});
+    uint32_t node;
+    memcpy(&node, slot + 16, 4);  // the first root: the first node
+    for (; node <= head[2]; ++node) {
+      uint32_t w[2];
+      memcpy(w, slot + 8 * (size_t)node, 8);
+      if ((w[0] >> 16) == 0x7FFFu) {
+        w[0] = (w[0] << 16) | 0xFFFFu;
+      } else {
+        const uint32_t left = node + ((w[0] >> 16) & 0x7FFFu), f = (w[0] >> 8) & 0xFFu;
+        const float t = float_of(w[1]);
+        const RankGrid &g = codes.grid[f];
+        const std::vector<float> &tab = codes.table[f];
+        const uint32_t code =  // x < t exactly when code(x) < code
+            g.top != 0.0f ? (uint32_t)((double)t * g.scale + g.bias)
+                          : (uint32_t)(std::lower_bound(tab.begin(), tab.end(), t) -
+                                       tab.begin()) + 1;
+        const bool default_left = (w[0] >> 31) != 0;
+        w[0] = (8u * left << 16) | (unit * (default_left ? code : code - 1));
+        w[1] = ((default_left ? unit : 0u) << 16) | codes.field[f].off;
+      }
+      memcpy(slot + 8 * (size_t)node, w, 8);
+    }
+  }
   return true;
 }
 

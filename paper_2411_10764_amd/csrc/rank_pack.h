@@ -74,7 +74,7 @@ struct RankGrid {     // per feature; top = 0: not a grid feature
   uint32_t put;
 };
 struct RankSeg {      // one table segment
-  uint32_t lane_reg;  // feature within its line
+  uint32_t lane_reg;  // bits 7..0 the feature within its line, 31..8 its thresholds here
   uint32_t put;       // kRankNone: a repeat that fills the group
   uint32_t table_off; // bytes from the start of the slot
   uint32_t steps;
@@ -122,5 +122,23 @@ bool rank_codes(const std::vector<TreeView> &views, int num_features, RankCodes 
 // trees of -0.0 leaves).  False where a group does not fit a slot.
 bool rank_pack(const std::vector<TreeView> &views, const RankCodes &codes, int num_features,
                int D, int group, uint32_t slot_bytes, RankPack *out);
+
+// Ragged trees (layout.h: default directions, any depth) over codes.  A
+// missing value has a code of its own, the largest of its width, so the codes
+// take a byte (up to 254 thresholds, missing 255) or 13 bits of a half-word,
+// shifted left by three (missing 8191).  Slots keep their headers, roots and
+// node order; a node becomes
+//   split  word 0 {byte offset of the left child, C}, word 1 {S, code offset}
+//   leaf   word 0 {byte offset of the next root, 0xFFFF}, word 1 the value
+// (high half, low half).  With y the code in the upper bits of 16 (a byte
+// shifted left by eight) and u its unit (256 or 8), a walk computes z = y + S
+// modulo 2^16 and goes right exactly when z > C: S = 0 and C = u (t - 1) send
+// a missing value right, S = u and C = u t wrap it to 0 and send it left.
+// z never exceeds 0xFFFF, so a leaf always takes its one way on.
+constexpr int kRankRaggedByte = 255, kRankRaggedHalf = 8191;  // the missing codes
+bool rank_pack_ragged(const RaggedPack &ragged, const RankCodes &codes, int num_features,
+                      RankPack *out);
+// The codes' places for ragged trees; false where a feature has too many.
+bool rank_ragged_fields(RankCodes *codes);
 
 }  // namespace ml2

@@ -47,6 +47,8 @@ struct RankArgs {
   int32_t nslots, nchunks, nlines, F;
   uint32_t slot_bytes, tile_bytes;
   int32_t nthreads;
+  uint32_t missing;  // ragged trees: a missing value's code, and
+  uint32_t off_mask;  // the bits of a code's offset in the tile
   int32_t vec4;  // rows load as 16-byte vectors (X aligned, ld % 4 == 0, F % 4 == 0)
   float base;
   uint8_t *valid_out;        // validity
@@ -57,6 +59,12 @@ struct RankArgs {
 
 // Registers (16 bytes each) per thread that stage one slot of at most 64 KiB.
 constexpr int rank_stage_regs(int waves) { return (64 + waves - 1) / waves; }
+// The same for a 24 KiB slot of ragged trees and the smallest workgroup of a
+// class: of 24 waves that share a CU twelve, of 16 eight, of 12 twelve, of 8
+// and of 4 four.
+constexpr int rank_ragged_stage_regs(int waves) {
+  return waves == 24 || waves == 12 ? 2 : waves == 16 ? 3 : 6;
+}
 
 
 namespace rank {
@@ -312,7 +320,7 @@ struct Slots {
     const u32x4 *src = reinterpret_cast<const u32x4 *>(a.slots + (size_t)s * a.slot_bytes);
 #pragma unroll
     for (int k = 0; k < R; ++k) {
-      if (R > 4 && (uint32_t)k * a.nthreads * 16u >= a.slot_bytes) break;
+      if ((uint32_t)k * a.nthreads * 16u >= a.slot_bytes) break;
       r[k] = src[threadIdx.x + (uint32_t)k * a.nthreads];
     }
   }
@@ -370,8 +378,9 @@ __device__ __forceinline__ void search4(const float (&x)[4], const uint32_t (&fi
 
 // Ranks the wave's rows into its tile; line[0] and line[1] hold their first
 // half-lines, and two stay in flight.  A wave without a row (not busy) only
-// keeps step with the slots.
-template <int R>
+// keeps step with the slots.  MISSING (ragged trees): a missing value takes a
+// code of its own.
+template <bool MISSING, int R>
 __device__ __forceinline__ void rank_rows(const RankArgs &a, const Rows &rows, Line (&line)[2],
                                           bool busy,
                                           uint32_t tile_lane, uint32_t buf, Slots<R> &st) {
@@ -391,7 +400,9 @@ __device__ __forceinline__ void rank_rows(const RankArgs &a, const Rows &rows, L
         const float s = grid[l * kRankLine + k].scale, b = grid[l * kRankLine + k].bias;
         const float c = __builtin_fmaxf(
             __builtin_fminf(__builtin_floorf(cur.v[k] * s) + b, top), 0.0f);
-        put_code(tile_lane, grid[l * kRankLine + k].put, (uint32_t)c);
+        uint32_t code = (uint32_t)c;
+        if (MISSING) code = __builtin_isnan(cur.v[k]) ? a.missing : code;
+        put_code(tile_lane, grid[l * kRankLine + k].put, code);
       }
     }
     const int g1 = line_group[l + 1];
@@ -409,6 +420,10 @@ __device__ __forceinline__ void rank_rows(const RankArgs &a, const Rows &rows, L
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const uint32_t put = groups[g].seg[i].put;
+        if (MISSING) {
+          count[i] = min(count[i], groups[g].seg[i].lane_reg >> 8);  // (not the padding)
+          count[i] = __builtin_isnan(x[i]) ? a.missing : count[i];
+        }
         if (put != kRankNone) put_code(tile_lane, put, count[i]);
       }
     }
@@ -427,29 +442,80 @@ __device__ __forceinline__ float walk_all(const RankArgs &a, bool busy, uint32_t
   return m;
 }
 
-// W: the most waves the launch uses (16, 12, 8 or 4), which sets the registers.
-template <int D, int G, RankMode M, int W, bool PERF>
-__global__ void __launch_bounds__(kLanes *W) __attribute__((amdgpu_waves_per_eu(W / 4, W / 4)))
-rank_kernel(RankArgs a) {
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  __shared__ int wave_count[kMaxWaves];
+// The performance walks' rows: the accepted rows of the pool, compacted into a
+// queue of 2 NT entries in LDS (NT: threads of the workgroup), NT at a time.
+struct Survivors {
+  int32_t *queue;
+  int *wave_count;
+  int64_t round, step, mine;  // the mask in units of 64 rows per wave, as in the validity walk
+  int qn, took;  // queued rows, and those the last next() took (the same in every thread)
+
+  __device__ __forceinline__ Survivors(const RankArgs &a, int32_t *q, int *counts)
+      : queue(q), wave_count(counts) {
+    const int lane = threadIdx.x & (kLanes - 1), wave = threadIdx.x / kLanes;
+    round = (int64_t)blockIdx.x * kLanes;
+    step = (int64_t)gridDim.x * a.nthreads;
+    mine = (int64_t)wave * gridDim.x * kLanes + lane;
+    qn = took = 0;
+  }
+  // Scans the mask NT entries at a time until NT rows are queued (or the pool
+  // is exhausted), then takes up to NT rows off the queue, which never holds
+  // more than 2 NT - 1.  Rejected rows get -inf.
+  __device__ __forceinline__ Rows next(const RankArgs &a) {
+    const int lane = threadIdx.x & (kLanes - 1), wave = threadIdx.x / kLanes;
+    const int NT = a.nthreads, nw = NT / kLanes;
+    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    while (qn < NT && round < a.n) {
+      const int64_t i = round + mine;
+      const bool in = i < a.n;
+      const bool v = in && (a.valid_in == nullptr || a.valid_in[i] != 0);
+      if (in && !v) __builtin_nontemporal_store(-INFINITY, a.score_out + i);
+      const uint64_t bal = __ballot(v);
+      if (lane == 0) wave_count[wave] = __popcll(bal);
+      __syncthreads();
+      int off = 0, tot = 0;
+      for (int w = 0; w < nw; ++w) {
+        const int c = wave_count[w];
+        off += (w < wave) ? c : 0;
+        tot += c;
+      }
+      if (v) queue[qn + off + __popcll(bal & below)] = (int32_t)i;
+      qn = __builtin_amdgcn_readfirstlane(qn + tot);
+      round += step;
+      __syncthreads();
+    }
+    const int take = min(qn, NT);
+    took = take;
+    Rows r;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int e = (int)(threadIdx.x & ~63u) + (lane & 15) + 16 * i;
+      r.r[i] = e < take ? queue[e] : -1;
+    }
+    const int rem = qn - take;  // < NT
+    const int32_t carry = ((int)threadIdx.x < rem) ? queue[take + threadIdx.x] : 0;
+    __syncthreads();
+    if ((int)threadIdx.x < rem) queue[threadIdx.x] = carry;
+    qn = rem;
+    __syncthreads();
+    return r;
+  }
+};
+
+// The round loops of a walk: `walk(busy)` folds every tree over the tile.
+template <bool PERF, bool MISSING, int R, typename Walk>
+__device__ __forceinline__ void rounds(const RankArgs &a, uint32_t tile_lane, uint32_t buf,
+                                       Slots<R> &st, int32_t *queue, int *wave_count,
+                                       Walk walk) {
   const int lane = threadIdx.x & (kLanes - 1);
-  const int wave = threadIdx.x / kLanes;
-  const int NT = a.nthreads;
-  const int nw = NT / kLanes;
-  Slots<rank_stage_regs(W)> st;
-  st.buf = smem + (size_t)nw * a.tile_bytes;
-  const uint32_t buf = lds_address(st.buf);
-  const uint32_t tile_lane = lds_address(smem) + (uint32_t)wave * a.tile_bytes + 4u * lane;
-  st.prime(a);
   Line line[2];
   if constexpr (!PERF) {
     // A round's rows of wave w of workgroup b: unit (round * nw + w) * grid +
     // b of 64 rows, so that the units spread evenly over the workgroups and a
     // short round leaves whole waves idle.
-    const int64_t step = (int64_t)gridDim.x * NT;
-    int64_t round = (int64_t)blockIdx.x * kLanes;                // wave 0's first row
-    const int64_t mine = (int64_t)wave * gridDim.x * kLanes;     // this wave's beyond it
+    const int64_t step = (int64_t)gridDim.x * a.nthreads;
+    int64_t round = (int64_t)blockIdx.x * kLanes;  // wave 0's first row
+    const int64_t mine = (int64_t)(threadIdx.x / kLanes) * gridDim.x * kLanes;
     auto rows_at = [&](int64_t first) {
       Rows w;
 #pragma unroll
@@ -465,12 +531,12 @@ rank_kernel(RankArgs a) {
     for (; round < a.n; round += step) {
       const int64_t first = round + mine;
       const bool busy = first < a.n;  // the same in every lane
-      rank_rows(a, rows, line, busy, tile_lane, buf, st);
+      rank_rows<MISSING>(a, rows, line, busy, tile_lane, buf, st);
       rows = rows_at(first + step);
       line[0].load(a, rows, 0);  // the next round's, in flight during the walk
       line[1].load(a, rows, 1);
       wave_sync();
-      const float m = walk_all<D, G, M>(a, busy, tile_lane, buf, st);
+      const float m = walk(busy);
       wave_sync();
       const int64_t row = first + lane;
       if (row < a.n) {
@@ -479,72 +545,44 @@ rank_kernel(RankArgs a) {
       }
     }
   } else {
-    int32_t *queue = reinterpret_cast<int32_t *>(st.buf + a.slot_bytes);  // 2 NT entries
-    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    // the mask in units of 64 rows per wave, as in the validity walk
-    const int64_t step = (int64_t)gridDim.x * NT;
-    int64_t round = (int64_t)blockIdx.x * kLanes;
-    const int64_t mine = (int64_t)wave * gridDim.x * kLanes + lane;
-    int qn = 0;    // queued rows (identical in every thread)
-    int took = 0;  // rows the last next_rows() took (identical in every thread)
-    // Scan the mask NT entries at a time until NT rows are queued (or the
-    // pool is exhausted), then take up to NT rows off the queue, which never
-    // holds more than 2 NT - 1.
-    auto next_rows = [&]() -> Rows {
-      while (qn < NT && round < a.n) {
-        const int64_t i = round + mine;
-        const bool in = i < a.n;
-        const bool v = in && (a.valid_in == nullptr || a.valid_in[i] != 0);
-        if (in && !v) __builtin_nontemporal_store(-INFINITY, a.score_out + i);
-        const uint64_t bal = __ballot(v);
-        if (lane == 0) wave_count[wave] = __popcll(bal);
-        __syncthreads();
-        int off = 0, tot = 0;
-        for (int w = 0; w < nw; ++w) {
-          const int c = wave_count[w];
-          off += (w < wave) ? c : 0;
-          tot += c;
-        }
-        if (v) queue[qn + off + __popcll(bal & below)] = (int32_t)i;
-        qn = __builtin_amdgcn_readfirstlane(qn + tot);
-        round += step;
-        __syncthreads();
-      }
-      const int take = min(qn, NT);
-      took = take;
-      Rows r;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int e = (int)(threadIdx.x & ~63u) + (lane & 15) + 16 * i;
-        r.r[i] = e < take ? queue[e] : -1;
-      }
-      const int rem = qn - take;  // < NT
-      const int32_t carry = ((int)threadIdx.x < rem) ? queue[take + threadIdx.x] : 0;
-      __syncthreads();
-      if ((int)threadIdx.x < rem) queue[threadIdx.x] = carry;
-      qn = rem;
-      __syncthreads();
-      return r;
-    };
-    Rows rows = next_rows();
-    int cur = took;  // rows of this round: the loop ends where there are none
+    Survivors sv(a, queue, wave_count);
+    Rows rows = sv.next(a);
+    int cur = sv.took;  // rows of this round: the loop ends where there are none
     line[0].load(a, rows, 0);
     line[1].load(a, rows, 1);
     while (cur != 0) {
       const bool busy = (int)(threadIdx.x & ~63u) < cur;  // the same in every lane
-      rank_rows(a, rows, line, busy, tile_lane, buf, st);
+      rank_rows<MISSING>(a, rows, line, busy, tile_lane, buf, st);
       const int32_t row = rows.own();
-      rows = next_rows();
-      const int ntook = took;
+      rows = sv.next(a);
       line[0].load(a, rows, 0);
-    line[1].load(a, rows, 1);
+      line[1].load(a, rows, 1);
       wave_sync();
-      const float m = walk_all<D, G, M>(a, busy, tile_lane, buf, st);
+      const float m = walk(busy);
       wave_sync();
       if (row >= 0) __builtin_nontemporal_store(m, a.score_out + row);
-      cur = ntook;
+      cur = sv.took;
     }
   }
+}
+
+// W: the most waves that share a CU (16, 12, 8 or 4), which sets the registers.
+template <int D, int G, RankMode M, int W, bool PERF>
+__global__ void __launch_bounds__(kLanes *W) __attribute__((amdgpu_waves_per_eu(W / 4, W / 4)))
+rank_kernel(RankArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  __shared__ int wave_count[kMaxWaves];
+  const int lane = threadIdx.x & (kLanes - 1);
+  const int wave = threadIdx.x / kLanes;
+  Slots<rank_stage_regs(W)> st;
+  st.buf = smem + (size_t)(a.nthreads / kLanes) * a.tile_bytes;
+  const uint32_t buf = lds_address(st.buf);
+  const uint32_t tile_lane = lds_address(smem) + (uint32_t)wave * a.tile_bytes + 4u * lane;
+  st.prime(a);
+  rounds<PERF, false>(a, tile_lane, buf, st, reinterpret_cast<int32_t *>(st.buf + a.slot_bytes),
+                      wave_count, [&](bool busy) {
+                        return walk_all<D, G, M>(a, busy, tile_lane, buf, st);
+                      });
 }
 
 // Trees walked together by a lane, per depth.
@@ -609,6 +647,8 @@ hipError_t launch(int depth, RankMode mode, int group, int waves, const RankArgs
 
 }  // namespace rank
 
+hipError_t launch_rank_ragged_kernel(bool perf, RankMode mode, int waves, const RankArgs &a,
+                                     int grid, size_t lds, hipStream_t s);
 hipError_t launch_rank_validity_kernel(int depth, RankMode mode, int group, int waves,
                                        const RankArgs &a, int grid, size_t lds, hipStream_t s);
 hipError_t launch_rank_perf_kernel(int depth, RankMode mode, int group, int waves, const RankArgs &a,

@@ -71,3 +71,32 @@ def test_perf_walk_without_mask():
     P = gen.perfect_ensemble(13, gen.STREAM_PERF, 200, 7, 40, 20, 0.1)
     V = gen.perfect_ensemble(13, gen.STREAM_VALIDITY, 8, 4, 40, 20, 0.5)
     check_pipeline(V, P, _rows(4, 5000, 40, 20), 16, perf_mask=False)
+
+
+# ragged trees: byte and half-word codes, one wave to several rounds, missing
+# values with both default directions, special values and thresholds
+@pytest.mark.parametrize("n", [1, 64, 65, 5000, 150001])
+@pytest.mark.parametrize("F,K,trees,depth", [
+    (40, 40, 90, 14),    # byte codes, grids only
+    (90, 30, 120, 14),   # byte codes, tables
+    (9, 0, 200, 12),     # half-word codes
+    (256, 100, 50, 20),  # widest rows
+])
+def test_ragged_perf_walk(n, F, K, trees, depth):
+    P = gen.ragged_ensemble(21, gen.STREAM_PERF, trees, depth, F, K, 0.1, max_nodes=255)
+    P = _with_special_thresholds(P, 7)
+    V = gen.perfect_ensemble(21, gen.STREAM_VALIDITY, 8, 4, F, K, 0.5)
+    X = _rows(n + 1, n, F, K)
+    X[np.random.default_rng(8).random(X.shape) < 0.05] = np.nan
+    check_pipeline(V, P, X, 16)
+
+
+@pytest.mark.parametrize("F,K,ld,offset", [(40, 40, 40, 0), (37, 10, 41, 1)])
+def test_ragged_validity_walk(F, K, ld, offset):
+    n = 200003
+    V = _with_special_thresholds(
+        gen.ragged_ensemble(22, gen.STREAM_VALIDITY, 60, 14, F, K, 0.5, max_nodes=255), 9)
+    P = gen.perfect_ensemble(22, gen.STREAM_PERF, 20, 5, F, K, 0.1)
+    X = _rows(5, n, F, K)
+    X[np.random.default_rng(9).random(X.shape) < 0.05] = np.nan
+    check_pipeline(V, P, X, 50, ld=ld, offset=offset)
