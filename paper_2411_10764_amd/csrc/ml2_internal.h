@@ -80,8 +80,9 @@ struct TreeView;
 struct RaggedPack;
 void rank_load(const std::vector<TreeView> &views, const RaggedPack *ragged, Forest *f);
 void rank_free(Forest *f);
-// Whether a walk of n_work rows (perf: the performance walk) takes the rank form.
-bool rank_takes(const Forest &f, int64_t n_work, int cu_count, bool perf);
+// Whether a walk of n_work rows (perf: the performance walk) takes the rank
+// form rather than the float walk of `plan`.
+bool rank_takes(const Forest &f, int64_t n_work, const WalkPlan &plan, bool perf);
 hipError_t launch_rank_validity(const Forest &f, const float *X, int64_t n, int64_t ld,
                                 uint8_t *valid_out, float *margin_out, int cu_count,
                                 hipStream_t s);

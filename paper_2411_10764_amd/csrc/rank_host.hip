@@ -119,21 +119,24 @@ void rank_load(const std::vector<TreeView> &views, const RaggedPack *ragged, For
     r.tile_bytes = codes.rows * kRankRow;
     if (!(ragged ? ragged_shape(r.tile_bytes, &r) : shape(r.tile_bytes, D, &r))) return;
     // Ranking a row costs about 0.8 of a node visit per search step and one
-    // per grid feature, and a visit of the rank walk takes about 0.3 of a
-    // visit less than one of the float walk, so small ensembles over many
-    // features keep the float walks (262,144 x 128, 40 trees of depth 4: 28
-    // us against 58; 16M x 128, 300 of depth 6: 7.84 ms against 7.0).  Deep
-    // trees and wide rows leave those few trees per lane or few waves
-    // (262,144 x 96, 100 trees of depth 10: 193 us against 101; 500,000 x
-    // 256, 100 of depth 12: 47.3 ms against 1.3).  A ragged tree's walk saves
-    // about nine such visits.
+    // per grid feature; a visit of the rank walk takes about 0.28 of a visit
+    // less than one of the float walk, 0.56 where that cannot prefetch its
+    // rows, and a ragged tree about nine visits less.  So small ensembles over
+    // many features keep the float walks (412,590 x 136, 42 trees of depth 4:
+    // 53 us against 109; 427,763 x 96, 190 of depth 6: 149 against 155; 16M x
+    // 128, 300 of depth 6: 7.84 ms against 7.0).  Trees of depth 9 and above
+    // leave those few trees per lane or few waves, and always rank (262,144 x
+    // 96, 100 trees of depth 10: 193 us against 101; 500,000 x 256, 100 of
+    // depth 12: 47.3 ms against 1.3).
     int64_t steps = 0, grids = 0;  // of ranking one row
     for (int32_t c = 0; c < f->num_features; ++c) {
       for (size_t n = codes.table[(size_t)c].size(); n; n >>= 1) ++steps;
       grids += codes.grid[(size_t)c].top != 0.0f;
     }
-    const int64_t saves = ragged ? 90 * (int64_t)f->num_trees : 3 * (int64_t)f->num_trees * D;
-    if ((ragged || (D < 9 && f->num_features <= 128)) && saves < 8 * steps + 10 * grids) return;
+    const bool prefetched = f->num_features <= 128 && f->num_features % 4 == 0;
+    const int64_t saves = ragged ? 450 * (int64_t)f->num_trees
+                                 : (prefetched ? 14 : 28) * (int64_t)f->num_trees * D;
+    if ((ragged || D < 9) && saves < 40 * steps + 50 * grids) return;
     RankPack p;
     if (!(ragged ? rank_pack_ragged(*ragged, codes, f->num_features, &p)
                  : rank_pack(views, codes, f->num_features, D, r.group, r.slot_bytes, &p)))
@@ -186,20 +189,24 @@ void rank_free(Forest *f) {
   f->rank = RankForm{};
 }
 
-// The performance walk always ranks where that pays (2,048 to 262,144 rows,
-// half of them accepted, five ensembles: 1.0 to 1.9 times faster).  The
-// validity walk does from three quarters of a round of every CU on: below
-// that the float walk's two lanes per candidate spread a short pool over more
-// of the chip (300 trees of depth 6 over 128 features: 65,536 rows 38 us
-// against 84, 262,144 rows 129 against 132, 16M rows 7.84 ms against 7.0;
-// 500 trees of depth 8 over 96: 131,072 rows 171 us against 164, 262,144 rows
-// 338 against 241).
-bool rank_takes(const Forest &f, int64_t n_work, int cu_count, bool perf) {
+// From three quarters of a round of every CU on (196,608 rows with 16 waves a
+// CU) a walk ranks where that pays.  Below, a walk takes as long as its
+// longest lane, and the float walk's two lanes per candidate and shorter
+// start win: validity, 300 trees of depth 6 over 128 features, 65,536 rows 38
+// us against 84, 262,144 rows 129 against 132, 16M rows 7.84 ms against 7.0;
+// performance, 177 trees of depth 7 over 76, 4,320 rows 28 us against 58.
+// Not so where the float walk's plan holds at most eight walks per lane column
+// (waves times trees per lane) and the pool has some rows per CU: 644 trees of
+// depth 10 over 112 features, 167,534 rows 1,040 us against 400; 499 over 159,
+// 54,335 rows 984 against 313; but 681 over 112 and 2,173 rows 362 against
+// 394.
+bool rank_takes(const Forest &f, int64_t n_work, const WalkPlan &plan, bool perf) {
   const RankForm &r = f.rank;
   if (!r.ok) return false;
   for (int t : {kTuneSplit, kTuneGroup, kTuneWaves, kTuneNbuf, kTuneChunk})
     if (get_tune(t) != 0) return false;  // the overrides shape the float walks
-  return perf || n_work >= (int64_t)48 * r.waves * r.per_cu * cu_count;
+  if (n_work >= (int64_t)48 * r.waves * r.per_cu * plan.cus) return true;
+  return perf && !f.ragged && plan.waves * plan.group <= 8 && n_work >= (int64_t)64 * plan.cus;
 }
 
 namespace {

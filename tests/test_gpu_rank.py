@@ -33,15 +33,16 @@ def _with_special_thresholds(ens, seed):
     return dataclasses.replace(ens, threshold=np.ascontiguousarray(thr, np.float32))
 
 
-# rows around one wave, one unit of each workgroup and one round; the mask of
-# a random validity model leaves the performance walk ragged rounds
-@pytest.mark.parametrize("n", [1, 63, 64, 65, 1000, 16385, 70001])
+# a round of the chip (196,608 rows with 256 compute units take the rank walk)
+# and some rows more; the mask of a random validity model leaves the
+# performance walk ragged rounds; few features keep the pools small
+@pytest.mark.parametrize("n", [196608, 196673, 270001])
 @pytest.mark.parametrize("F,K,depth,trees,special", [
     (24, 24, 6, 60, False),   # byte tile, grids only, no table
     (33, 8, 7, 150, True),    # byte tile or packed: tables with special thresholds
     (100, 50, 8, 300, False), # packed tile: 4-, 8- and 12-bit fields
     (3, 0, 10, 24, False),    # half-word tile: tables longer than a slot
-    (256, 128, 12, 3, True),  # widest rows, deepest trees, one tree per lane
+    (132, 100, 12, 3, True),  # wide rows, deepest trees, one tree per lane
 ])
 def test_perf_walk(n, F, K, depth, trees, special):
     P = gen.perfect_ensemble(11, gen.STREAM_PERF, trees, depth, F, K, 0.1)
@@ -67,20 +68,29 @@ def test_validity_walk(n, F, K, depth, trees, ld, offset):
     check_pipeline(V, P, _rows(3, n, F, K), 50, ld=ld, offset=offset)
 
 
+# a plan of few float walks per lane column ranks from 64 rows per CU on
+@pytest.mark.parametrize("n", [16384, 16385, 30011])
+def test_deep_perf_walk_of_a_short_pool(n):
+    P = gen.perfect_ensemble(14, gen.STREAM_PERF, 6, 12, 256, 128, 0.1)
+    V = gen.perfect_ensemble(14, gen.STREAM_VALIDITY, 8, 4, 256, 128, 0.5)
+    check_pipeline(V, _with_special_thresholds(P, 5), _rows(n, n, 256, 128), 16)
+
+
 def test_perf_walk_without_mask():
     P = gen.perfect_ensemble(13, gen.STREAM_PERF, 200, 7, 40, 20, 0.1)
     V = gen.perfect_ensemble(13, gen.STREAM_VALIDITY, 8, 4, 40, 20, 0.5)
-    check_pipeline(V, P, _rows(4, 5000, 40, 20), 16, perf_mask=False)
+    check_pipeline(V, P, _rows(4, 200000, 40, 20), 16, perf_mask=False)
 
 
-# ragged trees: byte and half-word codes, one wave to several rounds, missing
-# values with both default directions, special values and thresholds
-@pytest.mark.parametrize("n", [1, 64, 65, 5000, 150001])
+# ragged trees: byte and half-word codes, a part and more than one round (up to
+# 294,912 rows), missing values with both default directions, special values
+# and thresholds
+@pytest.mark.parametrize("n", [294912, 400001])
 @pytest.mark.parametrize("F,K,trees,depth", [
     (40, 40, 90, 14),    # byte codes, grids only
     (90, 30, 120, 14),   # byte codes, tables
     (9, 0, 200, 12),     # half-word codes
-    (256, 100, 50, 20),  # widest rows
+    (140, 100, 50, 20),  # wide rows
 ])
 def test_ragged_perf_walk(n, F, K, trees, depth):
     P = gen.ragged_ensemble(21, gen.STREAM_PERF, trees, depth, F, K, 0.1, max_nodes=255)
@@ -93,7 +103,7 @@ def test_ragged_perf_walk(n, F, K, trees, depth):
 
 @pytest.mark.parametrize("F,K,ld,offset", [(40, 40, 40, 0), (37, 10, 41, 1)])
 def test_ragged_validity_walk(F, K, ld, offset):
-    n = 200003
+    n = 300003
     V = _with_special_thresholds(
         gen.ragged_ensemble(22, gen.STREAM_VALIDITY, 60, 14, F, K, 0.5, max_nodes=255), 9)
     P = gen.perfect_ensemble(22, gen.STREAM_PERF, 20, 5, F, K, 0.1)
