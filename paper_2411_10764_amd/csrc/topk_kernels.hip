@@ -20,9 +20,9 @@
 //                or holds exactly the keys still needed; one last pass over
 //                the pool appends the keys above that bin (all selected) to
 //                one list and the keys in it to another;
-//   topk_finish  one workgroup: selects the needed keys of the bin in LDS
-//                (the same digit passes over the bin's keys), sorts the k
-//                selected keys (bitonic) and writes the outputs.
+//   topk_finish  a workgroup per 64 keys of the two lists: each key's place is
+//                the number of its list's keys above it; the selected ones
+//                are written there.
 // The grid barrier waits a bounded time (every workgroup of the launch can
 // be resident at once: the grid is at most one workgroup of 512 threads and
 // 16 KiB of LDS per CU); a wait
@@ -30,6 +30,7 @@
 // workgroup exits.
 #include <math.h>
 
+#include <algorithm>
 #include <mutex>
 #include <vector>
 
@@ -376,7 +377,7 @@ __global__ void __launch_bounds__(kSelThreads) topk_select(
     const uint8_t *valid, const float *scores, int64_t n, int32_t k, int vec,
     long long timeout_ticks, TopkState *st, uint32_t *hist, unsigned long long *take,
     unsigned long long *inbin) {
-  __shared__ uint32_t h[kBins];
+  __shared__ __align__(8) uint32_t h[kBins];
   __shared__ uint32_t wave_sum[kSelThreads / 64 + 1];
   __shared__ Pick pick_s;
   __shared__ int ok_s;
@@ -432,8 +433,37 @@ __global__ void __launch_bounds__(kSelThreads) topk_select(
     st->prefix = prefix;
     st->need_in = (int32_t)need;
   }
-  // the final pass: selected keys and the bin's keys, appended per wave;
-  // a group of 16 candidates of which no lane selects any costs one ballot
+  // The final pass: selected keys and the bin's keys.  A workgroup gathers
+  // them in LDS (the histogram's space) and appends them to the lists at its
+  // end, with one device-wide addition each: an addition per wave and group of
+  // 16 candidates that holds one queued up at the two counters (k = 2048 of
+  // 16M: 112 -> 71 us).  Keys past a full gather are appended directly.  A
+  // group of which no lane selects any costs one ballot.
+  constexpr int kGather = kBins * (int)sizeof(uint32_t) / 2 / (int)sizeof(unsigned long long);
+  unsigned long long *gather = reinterpret_cast<unsigned long long *>(h);  // selected, bin
+  __shared__ uint32_t gathered[2], base_s[2];
+  if (threadIdx.x < 2) gathered[threadIdx.x] = 0;
+  __syncthreads();
+  auto append = [&](int list, bool mine, unsigned long long key) {
+    const uint64_t b = __ballot(mine);
+    if (b == 0) return;
+    uint32_t p0 = 0;
+    if (lane == 0) p0 = atomicAdd(&gathered[list], (uint32_t)__popcll(b));
+    p0 = __shfl(p0, 0);
+    const uint32_t pos = p0 + (uint32_t)__popcll(b & below);
+    if (mine && pos < (uint32_t)kGather) gather[list * kGather + pos] = key;
+    const uint64_t rest = __ballot(mine && pos >= (uint32_t)kGather);
+    if (rest == 0) return;
+    uint32_t g0 = 0;
+    if (lane == 0)
+      g0 = atomicAdd(list == 0 ? &st->n_take : &st->n_in, (uint32_t)__popcll(rest));
+    g0 = __shfl(g0, 0);
+    const uint32_t at = g0 + (uint32_t)__popcll(rest & below);
+    if (mine && pos >= (uint32_t)kGather) {
+      if (list == 0 && at < (uint32_t)k) take[at] = key;
+      if (list == 1 && at < (uint32_t)kInCap) inbin[at] = key;
+    }
+  };
   for_each_tile(valid, scores, n, vec, [&](const bool *inc, const unsigned long long *key) {
     int cls[16];  // 1 selected, 2 in the bin
     bool any = false;
@@ -453,89 +483,110 @@ __global__ void __launch_bounds__(kSelThreads) topk_select(
     if (__ballot(any) == 0) return;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      const uint64_t b1 = __ballot(cls[e] == 1);
-      if (b1) {
-        uint32_t p0 = 0;
-        if (lane == 0) p0 = atomicAdd(&st->n_take, (uint32_t)__popcll(b1));
-        p0 = __shfl(p0, 0);
-        if (cls[e] == 1) {
-          const uint32_t pos = p0 + (uint32_t)__popcll(b1 & below);
-          if (pos < (uint32_t)k) take[pos] = key[e];
-        }
-      }
-      const uint64_t b2 = __ballot(cls[e] == 2);
-      if (b2) {
-        uint32_t p0 = 0;
-        if (lane == 0) p0 = atomicAdd(&st->n_in, (uint32_t)__popcll(b2));
-        p0 = __shfl(p0, 0);
-        if (cls[e] == 2) {
-          const uint32_t pos = p0 + (uint32_t)__popcll(b2 & below);
-          if (pos < (uint32_t)kInCap) inbin[pos] = key[e];
-        }
-      }
+      append(0, cls[e] == 1, key[e]);
+      append(1, cls[e] == 2, key[e]);
     }
   });
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    const uint32_t c = min(gathered[threadIdx.x], (uint32_t)kGather);
+    gathered[threadIdx.x] = c;
+    base_s[threadIdx.x] =
+        c ? atomicAdd(threadIdx.x == 0 ? &st->n_take : &st->n_in, c) : 0u;
+  }
+  __syncthreads();
+  for (uint32_t j = threadIdx.x; j < gathered[0]; j += T)
+    if (base_s[0] + j < (uint32_t)k) take[base_s[0] + j] = gather[j];
+  for (uint32_t j = threadIdx.x; j < gathered[1]; j += T)
+    if (base_s[1] + j < (uint32_t)kInCap) inbin[base_s[1] + j] = gather[kGather + j];
 }
 
-// One workgroup: the keys of the bin still needed (digit passes in LDS over
-// the bin's list), then the k selected keys sorted descending, then the
-// outputs.  keys: the selected keys (next power of two of k entries).
-__global__ void __launch_bounds__(kSortThreads) topk_finish(const float *scores, int64_t n,
+// The place of a key in its list, counted by a workgroup: sixteen threads per
+// key, each over a sixteenth of the list, which passes through LDS kRankTile
+// keys at a time.  Thread t has key x of entry (t & 63) of the workgroup;
+// returns the keys of list[0, m) above x, and with POS those equal to it at
+// earlier positions than `pos` (to all sixteen threads of the key; every thread
+// of the workgroup calls it).
+//
+// Why counting and not a sort: the sort of k keys is a chain of compare
+// exchanges in one workgroup, while the k * m comparisons spread over m / 64
+// workgroups and have no chain (selection of a 16M pool, k = 1024: 84 -> 75 us;
+// second level's 1,024 rows: 14 -> 5 us).
+constexpr int kRankThreads = 1024;
+constexpr int kRankKeys = 64;  // keys ranked by a workgroup
+constexpr int kRankParts = kRankThreads / kRankKeys;
+constexpr int kRankTile = 1024;
+template <bool POS, typename Get>
+__device__ __forceinline__ int count_above(Get get, int m, unsigned long long x, int pos,
+                                           unsigned long long *tile, int *sum) {
+  const int part = threadIdx.x >> 6, key = threadIdx.x & 63;
+  int above = 0;
+  for (int base = 0; base < m; base += kRankTile) {
+    const int left = m - base < kRankTile ? m - base : kRankTile;
+    static_assert(kRankTile == kRankThreads, "a thread stages one key of a tile");
+    const int j0 = (int)threadIdx.x;
+    const unsigned long long staged = j0 < left ? get(base + j0) : 0ull;  // no key is below 0
+    __syncthreads();
+    tile[j0] = staged;
+    __syncthreads();
+    const int per = (left + kRankParts - 1) / kRankParts;
+    const int lo = part * per, hi = lo + per < kRankTile ? lo + per : kRankTile;
+#pragma unroll 8
+    for (int j = lo; j < hi; ++j) {
+      // at an earlier position an equal key counts too
+      const unsigned long long y = (POS && base + j < pos) ? x - 1ull : x;
+      above += tile[j] > y ? 1 : 0;
+    }
+  }
+  __syncthreads();
+  sum[threadIdx.x] = above;
+  __syncthreads();
+  int all = 0;
+#pragma unroll
+  for (int p = 0; p < kRankParts; ++p) all += sum[p * kRankKeys + key];
+  return all;
+}
+
+// The outputs.  Workgroup w ranks keys [64 w, 64 w + 64) of the selected list
+// followed by the threshold bin's: a selected key's place is the number of
+// selected keys above it, a bin's key comes after all of them, at the number
+// of the bin's above it, and is selected if that is below need_in.
+__global__ void __launch_bounds__(kRankThreads) topk_finish(const float *scores, int64_t n,
                                                             const TopkState *st,
                                                             const unsigned long long *take,
                                                             const unsigned long long *inbin,
                                                             int32_t *idx, float *out,
                                                             int32_t *num) {
-  extern __shared__ unsigned long long keys[];
-  __shared__ uint32_t h[kBins];
-  __shared__ uint32_t wave_sum[kSortThreads / 64 + 1];
-  __shared__ Pick pick_s;
-  __shared__ uint32_t fill_s;
-  const int T = blockDim.x;
+  __shared__ unsigned long long tile[kRankTile];
+  __shared__ int sum[kRankThreads];
   const int k = st->k;
-  if (st->failed) {
-    for (int j = threadIdx.x; j < k; j += T) {
-      idx[j] = -1;
-      out[j] = -INFINITY;
-    }
-    if (threadIdx.x == 0) *num = -1;
-    return;
+  const int mode = st->failed ? 0 : st->mode;
+  const int cnt = mode == 0 ? 0 : min(k, st->total);
+  const int nt = mode == 0 ? 0 : (int)min(st->n_take, (uint32_t)k);
+  const int m = mode == kInBin ? (int)min(st->n_in, (uint32_t)kInCap) : 0;
+  for (int j = cnt + (int)(blockIdx.x * kRankThreads + threadIdx.x); j < k;
+       j += (int)gridDim.x * kRankThreads) {
+    idx[j] = -1;
+    out[j] = -INFINITY;
   }
-  const int mode = st->mode;
-  const int cnt = (mode == 0) ? 0 : min(k, st->total);
-  const int nt = (mode == 0) ? 0 : (int)min(st->n_take, (uint32_t)k);
-  const int size = sort_size(cnt);
-  for (int j = threadIdx.x; j < size; j += T) keys[j] = (j < nt) ? take[j] : 0ull;
-  if (mode == kInBin) {
-    // the need_in largest of the m keys of the bin, which share the top nbits
-    const int m = (int)min(st->n_in, (uint32_t)kInCap);
-    int nbits = st->nbits;
-    unsigned long long prefix = st->prefix;
-    select_in_block([&](int j) { return inbin[j]; }, m, (uint32_t)st->need_in, nbits, prefix, h,
-                    wave_sum, &pick_s);
-    if (threadIdx.x == 0) fill_s = 0;
-    __syncthreads();
-    for (int j = threadIdx.x; j < m; j += T) {
-      const unsigned long long key = inbin[j];
-      if ((key >> (64 - nbits)) >= prefix) {
-        const uint32_t pos = atomicAdd(&fill_s, 1u);
-        if (nt + (int)pos < size) keys[nt + pos] = key;
-      }
-    }
+  if (blockIdx.x == 0 && threadIdx.x == 0) *num = st->failed ? -1 : cnt;
+  // the workgroup's keys lie in one list: the bin's start at a multiple of 64
+  const int first = (int)blockIdx.x * kRankKeys, bin0 = (nt + kRankKeys - 1) / kRankKeys * kRankKeys;
+  const bool in_bin = first >= bin0;
+  const int e = first + (int)(threadIdx.x & 63) - (in_bin ? bin0 : 0);
+  const int len = in_bin ? m : nt;
+  if (first - (in_bin ? bin0 : 0) >= len) return;  // the same in every thread
+  const unsigned long long *list = in_bin ? inbin : take;
+  const unsigned long long x = e < len ? list[e] : 0ull;
+  const int above =
+      count_above<false>([&](int j) { return list[j]; }, len, x, 0, tile, sum);
+  const int place = (in_bin ? nt : 0) + above;
+  const int limit = in_bin ? min(cnt, nt + st->need_in) : cnt;
+  const int64_t i = (int64_t)(0xFFFFFFFFu - (uint32_t)(x & 0xFFFFFFFFull));
+  if (threadIdx.x < kRankKeys && e < len && place < limit && i < n) {
+    idx[place] = (int32_t)i;
+    out[place] = scores[i];
   }
-  __syncthreads();
-  block_sort_desc(keys, size);
-  for (int j = threadIdx.x; j < k; j += T) {
-    const int64_t i = (int64_t)(0xFFFFFFFFu - (uint32_t)(keys[j] & 0xFFFFFFFFull));
-    if (j < cnt && keys[j] != 0ull && i < n) {  // (always, for a selection that completed)
-      idx[j] = (int32_t)i;
-      out[j] = scores[i];
-    } else {
-      idx[j] = -1;
-      out[j] = -INFINITY;
-    }
-  }
-  if (threadIdx.x == 0) *num = cnt;
 }
 
 // Pools of at most kSmallN candidates, in one launch of one workgroup: the
@@ -639,15 +690,57 @@ __device__ __forceinline__ float row_key_score(unsigned long long key) {
   return (key & 1ull) ? -0.0f : key_score(key);
 }
 
-// Second-level selection (model A): one workgroup sorts the keys of the m
-// listed rows (row_key) and writes the best `keep`.  Rows outside [0, n)
-// and NaN scores are left out (key 0, below every included key: a zero high
-// word is the ord of a negative NaN).
-__global__ void __launch_bounds__(kSortThreads) rerank_select(const int32_t *rows,
+// Second-level selection (model A): workgroup w ranks list entries [64 w, 64 w
+// + 64) by their keys (row_key; equal keys, a row listed twice, in list
+// order) and writes those of the best `keep`.  Rows outside [0, n) and NaN
+// scores are left out (key 0, below every included key: a zero high word is
+// the ord of a negative NaN).
+__global__ void __launch_bounds__(kRankThreads) rerank_select(const int32_t *rows,
                                                               const float *scores, int32_t m,
                                                               int64_t n, int32_t keep,
                                                               int32_t *idx, float *out,
                                                               int32_t *num) {
+  __shared__ unsigned long long tile[kRankTile];
+  __shared__ int sum[kRankThreads];
+  __shared__ int included_s;
+  int mine = 0;  // included entries this thread has fetched
+  auto key_of = [&](int j) -> unsigned long long {
+    const int32_t r = rows[j];
+    const float sc = scores[j];
+    return (r >= 0 && r < n && !isnan(sc)) ? row_key(sc, r) : 0ull;
+  };
+  if (threadIdx.x == 0) included_s = 0;
+  const int e = (int)blockIdx.x * kRankKeys + (int)(threadIdx.x & 63);
+  const unsigned long long x = e < m ? key_of(e) : 0ull;
+  const int place = count_above<true>(
+      [&](int j) {
+        const unsigned long long key = key_of(j);
+        mine += key != 0ull ? 1 : 0;
+        return key;
+      },
+      m, x, e, tile, sum);
+  if (mine) atomicAdd(&included_s, mine);
+  __syncthreads();
+  const int cnt = min(included_s, keep);
+  if (threadIdx.x < kRankKeys && x != 0ull && place < cnt) {
+    idx[place] = row_key_row(x);
+    out[place] = row_key_score(x);
+  }
+  for (int j = cnt + (int)(blockIdx.x * kRankThreads + threadIdx.x); j < keep;
+       j += (int)gridDim.x * kRankThreads) {
+    idx[j] = -1;
+    out[j] = -INFINITY;
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) *num = cnt;
+}
+
+// The same in one workgroup that has read every entry before it writes one
+// (a bitonic sort in LDS): for outputs that share memory with the list.
+__global__ void __launch_bounds__(kSortThreads) rerank_select_one(const int32_t *rows,
+                                                                  const float *scores, int32_t m,
+                                                                  int64_t n, int32_t keep,
+                                                                  int32_t *idx, float *out,
+                                                                  int32_t *num) {
   extern __shared__ unsigned long long keys[];
   __shared__ int included_s;
   if (threadIdx.x == 0) included_s = 0;
@@ -719,61 +812,50 @@ __global__ void __launch_bounds__(256) held_reset(int32_t *held_id, float *held_
 // *c_n of them, chunk-local indices; pool row = row0 + index) by (P score
 // desc, pool row asc), a row present in both counted once.  Each entry
 // carries its P score and its second-level score (model A's, or P's again
-// when c_a is NULL), copied bit for bit.  One workgroup: keys
-// (ord(P) << 32) | (0xFFFFFFFF - row) and their source positions are sorted
-// together in LDS (bitonic, descending); equal keys are the same row with the
-// same score, so every key after an equal one is dropped.
+// when c_a is NULL), copied bit for bit.  One workgroup: both lists are sorted
+// by their keys (ord(P) << 32) | (0xFFFFFFFF - row) and have no key twice, so
+// an entry's place is its position in its own list plus the other list's keys
+// above it (a binary search in LDS), less the chunk's entries above it that
+// are held already (a prefix count); equal keys are the same row with the
+// same score, and the chunk's is dropped.
+__device__ __forceinline__ int keys_above(const unsigned long long *list, int n,
+                                          unsigned long long x) {
+  int lo = 0, len = n;
+  while (len > 0) {
+    const int half = (len + 1) >> 1;
+    lo = list[lo + half - 1] > x ? lo + half : lo;
+    len -= half;
+  }
+  return lo;
+}
+
 __global__ void __launch_bounds__(kSortThreads) merge_held(
     const int32_t *h_id, const float *h_p, const float *h_a, const int32_t *h_n,
     const int32_t *c_idx, const float *c_p, const float *c_a, const int32_t *c_n, int64_t row0,
     int32_t k, int32_t *o_id, float *o_p, float *o_a, int32_t *o_n) {
-  extern __shared__ unsigned long long keys[];
+  extern __shared__ unsigned long long keys[];  // held [k], chunk [k], then twins [k + 1]
   __shared__ int warp_sum[kSortThreads / 64 + 1];
-  int size = 1;
-  while (size < 2 * k) size <<= 1;
-  int32_t *pos = reinterpret_cast<int32_t *>(keys + size);
-  const int hn = min(*h_n, k), cn = min(*c_n, k);
-  for (int j = threadIdx.x; j < size; j += blockDim.x) {
-    unsigned long long key = 0ull;
-    if (j < hn) {
-      key = make_key(h_p[j], h_id[j]);
-    } else if (j >= k && j - k < cn) {
-      key = make_key(c_p[j - k], row0 + c_idx[j - k]);
-    }
-    keys[j] = key;
-    pos[j] = j;
-  }
+  unsigned long long *held = keys, *chunk = keys + k;
+  int32_t *twins = reinterpret_cast<int32_t *>(keys + 2 * k);  // chunk entries held, before j
+  const int hn = max(min(*h_n, k), 0), cn = max(min(*c_n, k), 0);
+  for (int j = threadIdx.x; j < hn; j += blockDim.x) held[j] = make_key(h_p[j], h_id[j]);
+  for (int j = threadIdx.x; j < cn; j += blockDim.x)
+    chunk[j] = make_key(c_p[j], row0 + c_idx[j]);
   __syncthreads();
-  for (int len = 2; len <= size; len <<= 1) {
-    for (int stride = len >> 1; stride > 0; stride >>= 1) {
-      for (int j = threadIdx.x; j < size; j += blockDim.x) {
-        const int p = j ^ stride;
-        if (p > j) {
-          const unsigned long long a = keys[j], b = keys[p];
-          const bool desc = (j & len) == 0;
-          if (desc ? (a < b) : (a > b)) {
-            keys[j] = b;
-            keys[p] = a;
-            const int32_t t = pos[j];
-            pos[j] = pos[p];
-            pos[p] = t;
-          }
-        }
-      }
-      __syncthreads();
-    }
-  }
-  // Rank of each first occurrence: each thread owns a run of consecutive
-  // sorted entries; the runs' counts are scanned across the workgroup.
-  const int per = size / blockDim.x > 0 ? size / blockDim.x : 1;
-  const int lo = threadIdx.x * per;
-  const bool owner = lo < size;
-  int mine = 0;
-  if (owner)
-    for (int j = lo; j < lo + per; ++j)
-      mine += (keys[j] != 0ull && (j == 0 || keys[j] != keys[j - 1])) ? 1 : 0;
-  // inclusive scan of `mine` over the threads: waves, then wave totals
+  // twins[j], by threads of four consecutive entries (k <= 4 * kSortThreads)
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lo = 4 * (int)threadIdx.x;
+  int twin[4], mine = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int j = lo + q;
+    twin[q] = 0;
+    if (j < cn) {
+      const int at = keys_above(held, hn, chunk[j]);
+      twin[q] = (at < hn && held[at] == chunk[j]) ? 1 : 0;
+    }
+    mine += twin[q];
+  }
   int incl = mine;
   for (int d = 1; d < 64; d <<= 1) {
     const int v = __shfl_up(incl, d);
@@ -791,34 +873,41 @@ __global__ void __launch_bounds__(kSortThreads) merge_held(
     warp_sum[blockDim.x >> 6] = acc;
   }
   __syncthreads();
-  const int unique = warp_sum[blockDim.x >> 6];
-  if (owner) {
-    int r = warp_sum[wave] + incl - mine;  // rank of this run's first occurrence
-    for (int j = lo; j < lo + per; ++j) {
-      if (keys[j] == 0ull || (j > 0 && keys[j] == keys[j - 1])) continue;
-      if (r < k) {
-        const int src = pos[j];
-        if (src < k) {
-          o_id[r] = h_id[src];
-          o_p[r] = h_p[src];
-          o_a[r] = h_a[src];
-        } else {
-          const int c = src - k;
-          o_id[r] = (int32_t)(row0 + c_idx[c]);
-          o_p[r] = c_p[c];
-          o_a[r] = c_a ? c_a[c] : c_p[c];
-        }
-      }
-      ++r;
+  int before = warp_sum[wave] + incl - mine;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    if (lo + q < k) twins[lo + q] = before;
+    before += twin[q];
+  }
+  const int all_twins = warp_sum[blockDim.x >> 6];
+  if (threadIdx.x == 0) twins[k] = all_twins;
+  __syncthreads();
+  for (int j = threadIdx.x; j < hn; j += blockDim.x) {
+    const int above = keys_above(chunk, cn, held[j]);
+    const int r = j + above - (above < cn ? twins[above] : all_twins);
+    if (r < k) {
+      o_id[r] = h_id[j];
+      o_p[r] = h_p[j];
+      o_a[r] = h_a[j];
     }
   }
-  const int held = min(unique, k);
-  for (int r = held + threadIdx.x; r < k; r += blockDim.x) {
+  for (int j = threadIdx.x; j < cn; j += blockDim.x) {
+    const int above = keys_above(held, hn, chunk[j]);
+    if (above < hn && held[above] == chunk[j]) continue;  // held already
+    const int r = j - twins[j] + above;
+    if (r < k) {
+      o_id[r] = (int32_t)(row0 + c_idx[j]);
+      o_p[r] = c_p[j];
+      o_a[r] = c_a ? c_a[j] : c_p[j];
+    }
+  }
+  const int total = min(hn + cn - all_twins, k);
+  for (int r = total + (int)threadIdx.x; r < k; r += blockDim.x) {
     o_id[r] = -1;
     o_p[r] = -INFINITY;
     o_a[r] = -INFINITY;
   }
-  if (threadIdx.x == 0) *o_n = held;
+  if (threadIdx.x == 0) *o_n = total;
 }
 
 }  // namespace
@@ -926,10 +1015,9 @@ hipError_t launch_topk(const uint8_t *valid, const float *scores, int64_t n, int
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  const size_t lds = (size_t)sort_size(k) * sizeof(unsigned long long);
-  e = ensure_dynamic_lds(reinterpret_cast<const void *>(&topk_finish), lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(topk_finish, dim3(1), dim3(kSortThreads), lds, s, scores, n, st, take,
+  // a workgroup per 64 selected keys (at most k) and per 64 of the bin's
+  const unsigned finish = (unsigned)((k + kRankKeys - 1) / kRankKeys + kInCap / kRankKeys);
+  hipLaunchKernelGGL(topk_finish, dim3(finish), dim3(kRankThreads), 0, s, scores, n, st, take,
                      inbin, idx, score, num);
   return hipGetLastError();
 }
@@ -937,11 +1025,26 @@ hipError_t launch_topk(const uint8_t *valid, const float *scores, int64_t n, int
 hipError_t launch_rerank_select(const int32_t *rows, const float *scores, int32_t m, int64_t n,
                                 int32_t keep, int32_t *idx, float *score, int32_t *num,
                                 hipStream_t s) {
-  const size_t lds = (size_t)sort_size(m) * sizeof(unsigned long long);
-  hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(&rerank_select), lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(rerank_select, dim3(1), dim3(kSortThreads), lds, s, rows, scores, m, n, keep,
-                     idx, score, num);
+  auto overlap = [](const void *a, size_t na, const void *b, size_t nb) {
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return x < y + nb && y < x + na;
+  };
+  const size_t in = 4 * (size_t)m, outs = 4 * (size_t)keep;
+  bool shared = false;
+  for (const void *list : {static_cast<const void *>(rows), static_cast<const void *>(scores)})
+    shared = shared || overlap(list, in, idx, outs) || overlap(list, in, score, outs) ||
+             overlap(list, in, num, 4);
+  if (shared) {
+    const size_t lds = (size_t)sort_size(m) * sizeof(unsigned long long);
+    hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(&rerank_select_one), lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(rerank_select_one, dim3(1), dim3(kSortThreads), lds, s, rows, scores, m, n,
+                       keep, idx, score, num);
+    return hipGetLastError();
+  }
+  const unsigned grid = (unsigned)std::max(1, (m + kRankKeys - 1) / kRankKeys);
+  hipLaunchKernelGGL(rerank_select, dim3(grid), dim3(kRankThreads), 0, s, rows, scores, m, n,
+                     keep, idx, score, num);
   return hipGetLastError();
 }
 
@@ -969,9 +1072,7 @@ hipError_t launch_held_reset(int32_t *held_id, float *held_p, float *held_a, int
 }
 
 size_t merge_held_lds(int32_t k) {
-  int size = 1;
-  while (size < 2 * k) size <<= 1;
-  return (size_t)size * (sizeof(unsigned long long) + sizeof(int32_t));
+  return (size_t)k * (2 * sizeof(unsigned long long) + sizeof(int32_t)) + sizeof(int64_t);
 }
 
 hipError_t launch_merge_held(const int32_t *h_id, const float *h_p, const float *h_a,

@@ -97,6 +97,7 @@ struct WalkArgs {
   const char *trees2;       // one pass over the pool: model P's records
   int32_t ntrees2;          // its trees (V's are the first fold_trees of the list)
   float base2;              // its margin bias
+  int32_t share;            // leaf walk of ragged slots: waves that take one tile's groups
 };
 
 // Row `row` of X into the tile of its candidate (dst = tile + 4*candidate),
@@ -1359,13 +1360,18 @@ fused_kernel(WalkArgs a) {
 // (lane = entry) and writes the leaf each of its trees gives each entry to
 // leaves_out[t * n + entry].  fold_kernel then adds them up in tree order, so
 // a list of a few rows still spreads over the whole GPU.
+// Ragged slots hold many groups of trees: `share` waves then take one tile's
+// groups in turn (the second level of 20 rows, 300 trees of depth up to 14: 36
+// -> 16 us).
 template <int D, int G>
-__global__ void __launch_bounds__(kLanes * 4) leaves_kernel(WalkArgs a) {
+__global__ void __launch_bounds__(kLanes *(D == 0 ? 16 : 4)) leaves_kernel(WalkArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   constexpr uint32_t RB = record_bytes(D);
   const int lane = threadIdx.x & (kLanes - 1);
-  const int wave = threadIdx.x / kLanes;
-  const int W = a.nthreads / kLanes;
+  const int share = D == 0 ? a.share : 1;                // waves per tile
+  const int wave = (int)(threadIdx.x / kLanes) / share;  // tile
+  const int part = (int)(threadIdx.x / kLanes) % share;
+  const int W = a.nthreads / kLanes / share;
   const size_t tile_bytes = (size_t)a.F * Geo<1>::kRowBytes;
   char *chunk = smem + W * tile_bytes;
   const int r0 = blockIdx.x * a.chunk_trees;         // first record
@@ -1380,7 +1386,7 @@ __global__ void __launch_bounds__(kLanes * 4) leaves_kernel(WalkArgs a) {
     if (r >= 0 && r < a.n_pool) row = r;
   }
   char *tile_lane = smem + wave * tile_bytes + 4 * lane;
-  if (row >= 0) load_row<1>(a, row, tile_lane);
+  if (row >= 0 && part == 0) load_row<1>(a, row, tile_lane);
   __syncthreads();
   // the leaves of trees t .. t+G-1 of the ensemble
   auto store = [&](int t, const auto &A, const auto &B) {
@@ -1399,7 +1405,7 @@ __global__ void __launch_bounds__(kLanes * 4) leaves_kernel(WalkArgs a) {
       const char *slot = chunk + (uint32_t)i * RB;
       const SlotHead hd = slot_head(slot);
       const uint32_t *roots = reinterpret_cast<const uint32_t *>(slot + 16);
-      for (int g0 = 0; g0 < hd.ntrees; g0 += G)
+      for (int g0 = part * G; g0 < hd.ntrees; g0 += share * G)
         walk_group_ragged<G, 1>(slot, roots + g0, hd.depth, tile_lane,
                                 [&](const auto &A, const auto &B) { store(hd.tree0 + g0, A, B); });
     }
@@ -1410,19 +1416,72 @@ __global__ void __launch_bounds__(kLanes * 4) leaves_kernel(WalkArgs a) {
   }
 }
 
-// score_out[i] = base + leaf_0 + leaf_1 + ... (float32, tree order) for list
-// entries whose row is in the pool, -inf for the others.
-__global__ void __launch_bounds__(256) fold_kernel(WalkArgs a) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= a.n) return;
-  const int32_t r = a.rows_in[i];
-  if (r < 0 || r >= a.n_pool) {
-    a.score_out[i] = -INFINITY;
-    return;
+// The same for deep perfect trees: workgroup (t, r) stages tree t alone and
+// walks list entries [r*64W, (r+1)*64W) through it, each lane reading its
+// row's features where they lie.  A tile of 128 features takes 32 KiB per wave
+// and a tree of depth 12 48 KiB, so a workgroup of tiles held three waves and
+// staged every tree for 192 entries; here sixteen waves share one staged tree
+// and hide their gathers (2,048 entries of an 8M x 128 pool, 300 trees of
+// depth 12, the second level: 228 -> 108 us; a list's rows stay in L2).
+__global__ void __launch_bounds__(kLanes * 16) leaves_gather_kernel(WalkArgs a, int depth) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const uint32_t rb = record_bytes(depth);
+  const uint32_t L = 1u << depth;
+  const u32x4 *src = reinterpret_cast<const u32x4 *>(a.trees + (size_t)blockIdx.x * rb);
+  for (uint32_t i = threadIdx.x; i < rb / 16u; i += a.nthreads)
+    reinterpret_cast<u32x4 *>(smem)[i] = src[i];
+  const int64_t pos = (int64_t)blockIdx.y * a.nthreads + threadIdx.x;
+  int64_t row = -1;
+  if (pos < a.n) {
+    const int32_t r = a.rows_in[pos];
+    if (r >= 0 && r < a.n_pool) row = r;
   }
+  const float *x = a.X + (row >= 0 ? row : 0) * a.ld;
+  __syncthreads();
+  if (row < 0) return;
+  uint32_t u = 1u;
+  for (int l = 0; l < depth; ++l) {
+    const uint2 nd = *reinterpret_cast<const uint2 *>(smem + 8u * u);
+    u = 2u * u + (x[nd.x] < __uint_as_float(nd.y) ? 1u : 0u);
+  }
+  a.leaves_out[(size_t)blockIdx.x * a.n + pos] =
+      *reinterpret_cast<const float *>(smem + 4u * L + 4u * u);
+}
+
+// score_out[i] = base + leaf_0 + leaf_1 + ... (float32, tree order) for list
+// entries whose row is in the pool, -inf for the others.  A workgroup folds 64
+// entries: its 16 waves fetch a tile of 16 kFoldRegs trees' leaves each, all
+// in flight at once, and the first wave adds them up from LDS (one thread's
+// own loads, an entry at a time, waited for each: 300 trees 78 us; so 5).
+constexpr int kFoldWaves = 16;
+constexpr int kFoldRegs = 8;
+__global__ void __launch_bounds__(kLanes *kFoldWaves) fold_kernel(WalkArgs a) {
+  constexpr int TILE = kFoldWaves * kFoldRegs;  // trees
+  __shared__ float leaf[TILE][kLanes];
+  const int lane = threadIdx.x & (kLanes - 1);
+  const int wave = threadIdx.x / kLanes;
+  const int64_t i = (int64_t)blockIdx.x * kLanes + lane;
   float m = a.base;
-  for (int t = 0; t < a.fold_trees; ++t) m = m + a.leaves_out[(size_t)t * a.n + i];
-  a.score_out[i] = m;
+  for (int t0 = 0; t0 < a.fold_trees; t0 += TILE) {
+    float v[kFoldRegs];
+#pragma unroll
+    for (int q = 0; q < kFoldRegs; ++q) {
+      const int t = t0 + q * kFoldWaves + wave;
+      v[q] = (t < a.fold_trees && i < a.n) ? a.leaves_out[(size_t)t * a.n + i] : -0.0f;
+    }
+    __syncthreads();  // the first wave is done with the tile before
+#pragma unroll
+    for (int q = 0; q < kFoldRegs; ++q) leaf[q * kFoldWaves + wave][lane] = v[q];
+    __syncthreads();
+    if (wave == 0) {
+      const int nt = min(TILE, a.fold_trees - t0);
+#pragma unroll 16
+      for (int t = 0; t < nt; ++t) m = m + leaf[t][lane];
+    }
+  }
+  if (wave != 0 || i >= a.n) return;
+  const int32_t r = a.rows_in[i];
+  a.score_out[i] = (r >= 0 && r < a.n_pool) ? m : -INFINITY;
 }
 
 // Trees walked concurrently per lane that a depth allows.  S = 1: a chunk
@@ -1564,45 +1623,45 @@ hipError_t launch_walk(bool perf, const Forest &f, const WalkPlan &p, const Walk
 }
 
 template <int D, int G>
-hipError_t launch_leaves_dg(const WalkArgs &a, int W, size_t lds, int row_tiles, hipStream_t s) {
+hipError_t launch_leaves_dg(const WalkArgs &a, size_t lds, int row_tiles, hipStream_t s) {
   const void *fn = reinterpret_cast<const void *>(&leaves_kernel<D, G>);
   hipError_t e = ensure_dynamic_lds(fn, lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((leaves_kernel<D, G>), dim3((unsigned)a.nchunks, (unsigned)row_tiles),
-                     dim3(W * kLanes), lds, s, a);
+                     dim3(a.nthreads), lds, s, a);
   return hipGetLastError();
 }
 
 template <int D>
-hipError_t launch_leaves_depth(const WalkArgs &a, int G, int W, size_t lds, int row_tiles,
+hipError_t launch_leaves_depth(const WalkArgs &a, int G, size_t lds, int row_tiles,
                                hipStream_t s) {
   switch (G) {
-    case 1: if constexpr (group_allowed(D, 1, 1)) return launch_leaves_dg<D, 1>(a, W, lds, row_tiles, s); break;
-    case 2: if constexpr (group_allowed(D, 2, 1)) return launch_leaves_dg<D, 2>(a, W, lds, row_tiles, s); break;
-    case 4: if constexpr (group_allowed(D, 4, 1)) return launch_leaves_dg<D, 4>(a, W, lds, row_tiles, s); break;
-    case 8: if constexpr (group_allowed(D, 8, 1)) return launch_leaves_dg<D, 8>(a, W, lds, row_tiles, s); break;
-    case 16: if constexpr (group_allowed(D, 16, 1)) return launch_leaves_dg<D, 16>(a, W, lds, row_tiles, s); break;
+    case 1: if constexpr (group_allowed(D, 1, 1)) return launch_leaves_dg<D, 1>(a, lds, row_tiles, s); break;
+    case 2: if constexpr (group_allowed(D, 2, 1)) return launch_leaves_dg<D, 2>(a, lds, row_tiles, s); break;
+    case 4: if constexpr (group_allowed(D, 4, 1)) return launch_leaves_dg<D, 4>(a, lds, row_tiles, s); break;
+    case 8: if constexpr (group_allowed(D, 8, 1)) return launch_leaves_dg<D, 8>(a, lds, row_tiles, s); break;
+    case 16: if constexpr (group_allowed(D, 16, 1)) return launch_leaves_dg<D, 16>(a, lds, row_tiles, s); break;
     default: break;
   }
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_leaves(int depth, const WalkArgs &a, int G, int W, size_t lds, int row_tiles,
+hipError_t launch_leaves(int depth, const WalkArgs &a, int G, size_t lds, int row_tiles,
                          hipStream_t s) {
   switch (depth) {
-    case 0: return launch_leaves_depth<0>(a, G, W, lds, row_tiles, s);
-    case 1: return launch_leaves_depth<1>(a, G, W, lds, row_tiles, s);
-    case 2: return launch_leaves_depth<2>(a, G, W, lds, row_tiles, s);
-    case 3: return launch_leaves_depth<3>(a, G, W, lds, row_tiles, s);
-    case 4: return launch_leaves_depth<4>(a, G, W, lds, row_tiles, s);
-    case 5: return launch_leaves_depth<5>(a, G, W, lds, row_tiles, s);
-    case 6: return launch_leaves_depth<6>(a, G, W, lds, row_tiles, s);
-    case 7: return launch_leaves_depth<7>(a, G, W, lds, row_tiles, s);
-    case 8: return launch_leaves_depth<8>(a, G, W, lds, row_tiles, s);
-    case 9: return launch_leaves_depth<9>(a, G, W, lds, row_tiles, s);
-    case 10: return launch_leaves_depth<10>(a, G, W, lds, row_tiles, s);
-    case 11: return launch_leaves_depth<11>(a, G, W, lds, row_tiles, s);
-    case 12: return launch_leaves_depth<12>(a, G, W, lds, row_tiles, s);
+    case 0: return launch_leaves_depth<0>(a, G, lds, row_tiles, s);
+    case 1: return launch_leaves_depth<1>(a, G, lds, row_tiles, s);
+    case 2: return launch_leaves_depth<2>(a, G, lds, row_tiles, s);
+    case 3: return launch_leaves_depth<3>(a, G, lds, row_tiles, s);
+    case 4: return launch_leaves_depth<4>(a, G, lds, row_tiles, s);
+    case 5: return launch_leaves_depth<5>(a, G, lds, row_tiles, s);
+    case 6: return launch_leaves_depth<6>(a, G, lds, row_tiles, s);
+    case 7: return launch_leaves_depth<7>(a, G, lds, row_tiles, s);
+    case 8: return launch_leaves_depth<8>(a, G, lds, row_tiles, s);
+    case 9: return launch_leaves_depth<9>(a, G, lds, row_tiles, s);
+    case 10: return launch_leaves_depth<10>(a, G, lds, row_tiles, s);
+    case 11: return launch_leaves_depth<11>(a, G, lds, row_tiles, s);
+    case 12: return launch_leaves_depth<12>(a, G, lds, row_tiles, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1918,6 +1977,18 @@ size_t rows_workspace_bytes(const Forest &f, int32_t m) {
   return (b + 255) & ~(size_t)255;
 }
 
+// Perfect trees from this depth on are walked one per workgroup with their
+// rows' features gathered (leaves_gather_kernel).  The second level of 300
+// trees over 1,024 rows of an 8M x 128 pool, tiles against gathers: depth 12
+// 124 and 75 us, depth 10 74 and 64; 200 of depth 9 39 and 39.
+constexpr int kGatherDepth = 10;
+
+static hipError_t launch_fold(const WalkArgs &a, hipStream_t s) {
+  hipLaunchKernelGGL(fold_kernel, dim3((unsigned)((a.n + kLanes - 1) / kLanes)),
+                     dim3(kLanes * kFoldWaves), 0, s, a);
+  return hipGetLastError();
+}
+
 // Tree-parallel walk of m listed rows: W waves of 64 entries per workgroup
 // (as many as the list needs, at most four, fewer if the tiles and G trees
 // do not fit), chunks of whole trees sized so the grid holds about two
@@ -1927,6 +1998,29 @@ hipError_t launch_rows(const Forest &f, const float *X, int64_t n, int64_t ld, c
   if (m <= 0) return hipSuccess;
   const size_t rb = f.rec_bytes;
   const int D = f.ragged ? 0 : f.depth;
+  if (D >= kGatherDepth) {
+    WalkArgs a{};
+    a.X = X;
+    a.n = m;
+    a.n_pool = n;
+    a.ld = ld;
+    a.trees = static_cast<const char *>(f.d_trees);
+    a.nthreads = (int)std::min<int64_t>(16, (m + kLanes - 1) / kLanes) * kLanes;
+    a.base = f.base;
+    a.rows_in = rows;
+    a.score_out = score_out;
+    a.leaves_out = static_cast<float *>(ws);
+    a.fold_trees = f.num_trees_padded;
+    hipError_t e =
+        ensure_dynamic_lds(reinterpret_cast<const void *>(&leaves_gather_kernel), rb);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(leaves_gather_kernel,
+                       dim3((unsigned)f.records, (unsigned)((m + a.nthreads - 1) / a.nthreads)),
+                       dim3(a.nthreads), rb, s, a, D);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return launch_fold(a, s);
+  }
   const size_t tile = (size_t)f.num_features * Geo<1>::kRowBytes;
   int W = (int)std::min<int64_t>(4, (m + kLanes - 1) / kLanes);
   int G = 0;
@@ -1960,17 +2054,18 @@ hipError_t launch_rows(const Forest &f, const float *X, int64_t n, int64_t ld, c
   a.nchunks = (tpad + ct - 1) / ct;
   a.F = f.num_features;
   a.vec4 = ((reinterpret_cast<uintptr_t>(X) & 15u) == 0 && (ld & 3) == 0) ? 1 : 0;
-  a.nthreads = W * kLanes;
+  // a slot of 24 KiB rarely holds more than eight groups of trees
+  a.share = f.ragged ? std::max(1, std::min(8, 16 / W)) : 1;
+  a.nthreads = W * kLanes * a.share;
   a.base = f.base;
   a.rows_in = rows;
   a.score_out = score_out;
   a.leaves_out = static_cast<float *>(ws);
   a.fold_trees = f.num_trees_padded;
   const size_t lds = W * tile + (size_t)ct * rb;
-  hipError_t e = launch_leaves(D, a, G, W, lds, row_tiles, s);
+  hipError_t e = launch_leaves(D, a, G, lds, row_tiles, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(fold_kernel, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, a);
-  return hipGetLastError();
+  return launch_fold(a, s);
 }
 
 template <int D, int G, int S>
