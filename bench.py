@@ -33,8 +33,10 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
-# Node-visit ceiling of the chip, from its unit counts and clock (256 CUs,
-# 2.4 GHz).  A visit needs, per lane, two LDS reads (the 8-byte node and the
+# Node-visit ceiling of the chip for the float walks, from its unit counts and
+# clock (256 CUs, 2.4 GHz); large pools are walked over threshold codes
+# (rank_walk.h), whose nodes take 4 bytes and codes 1 or 2, and are reported
+# against the same ceiling.  A float visit needs, per lane, two LDS reads (the 8-byte node and the
 # 4-byte feature value) and, as counted on the walks (SQ_INSTS_VALU per
 # wave-visit: 5.01 in the perf walk, 5.27 in the validity walk), five VALU
 # instructions (node address, feature address, the comparison
@@ -46,8 +48,9 @@ HBM_PEAK_GBS = 8000.0
 #         consecutive 16-byte read probe of --probe reaches 156 B/clk)
 #         -> 157 TB/s / 12 B = 13.1 T visits/s.
 # The lower one, the LDS ceiling, is the peak.  Beside it the line carries
-# the walk loop's measured rate at the perf walk's shape (the probe of
-# --probe: the same loop over a resident chunk, no row loads or restaging).
+# the float walk loop's measured rate at the shape a float walk of the pool
+# takes (the probe of --probe: the loop over a resident chunk, no row loads or
+# restaging).
 VALU_LANE_OPS_PER_S = 256 * 128 * 2.4e9
 VALU_PER_VISIT = 5
 VISIT_PEAK_VALU = VALU_LANE_OPS_PER_S / VALU_PER_VISIT
@@ -55,12 +58,12 @@ LDS_BYTES_PER_S = 256 * 256 * 2.4e9
 VISIT_PEAK_LDS = LDS_BYTES_PER_S / 12
 VISIT_PEAK_PER_S = min(VISIT_PEAK_VALU, VISIT_PEAK_LDS)
 MALL_BYTES = 256 << 20  # MI355X Infinity Cache: pools below it are flushed between steps
-# The perf walk's launch shape (depth, trees per lane, lanes per candidate,
+# The float perf walk's launch shape (depth, trees per lane, lanes per candidate,
 # waves, features) where the walk-loop probe is built for it: the 16M pool,
 # the explorer workload (64 visible columns) and the Skewed pool (depth 10).
 PERF_WALK_SHAPE = {"roofline": (8, 4, 2, 8, 128), "explorer": (8, 8, 1, 8, 64),
                    "skewed": (10, 4, 1, 6, 64)}
-# The validity walk's launch shape on the same pools.
+# The float validity walk's launch shape on the same pools.
 VALIDITY_WALK_SHAPE = {"roofline": (6, 8, 2, 8, 128), "explorer": (6, 8, 1, 8, 64),
                        "skewed": (6, 8, 1, 8, 64)}
 METRIC = "candidate configs scored+filtered/sec (validity+perf+top-k); % of HBM peak"
@@ -651,7 +654,7 @@ def main() -> int:
         "bound": "alu",
         "limiter": "lds",
         "kernel": ("fused_kernel (V then P on every row, one pass over the pool)" if fused
-                   else "perf_kernel (model P walk over accepted candidates)"),
+                   else "performance walk (model P over accepted candidates)"),
         "peak_derivation": "node visits on chip (LDS + VALU, no HBM or MFMA term): LDS 256 "
                            "B/clk/CU x 256 CU x 2.4 GHz / 12 B per visit = "
                            f"{VISIT_PEAK_LDS / 1e12:.1f} T/s; VALU 128 lanes/clk/CU x 256 CU x "
@@ -670,7 +673,7 @@ def main() -> int:
         "launch_ms": t_perf,
         "measured_ceiling": ({"achieved": loop / 1e12,
                               "frac": perf_visits_per_s / loop,
-                              "what": "walk loop alone at the perf walk's shape "
+                              "what": "float walk loop alone at a float perf walk's shape "
                                       f"(depth {shape[0]}, {shape[1]} trees per lane, {shape[2]} "
                                       f"lanes per candidate, {shape[3]} waves, {shape[4]} "
                                       "features; ml2_probe_visit, timed live)"}
@@ -680,7 +683,7 @@ def main() -> int:
                              "frac": v_visits_per_s / VISIT_PEAK_PER_S,
                              "measured_ceiling": (
                                  {"achieved": vloop / 1e12, "frac": v_visits_per_s / vloop,
-                                  "what": "walk loop alone at the validity walk's shape "
+                                  "what": "float walk loop alone at a float validity walk's shape "
                                           f"(depth {vshape[0]}, {vshape[1]} trees per lane, "
                                           f"{vshape[2]} lanes per candidate, {vshape[3]} waves, "
                                           f"{vshape[4]} features)"} if vloop else None)}),

@@ -90,6 +90,9 @@ typedef struct ml2_ensemble ml2_ensemble; /* opaque; immutable after load */
  * four times their node count; the others are packed tree by tree into
  * 24 KiB chunks, which holds trees of at most ML2_MAX_TREE_NODES nodes
  * (Table 3's depth-14 models trained on the paper's data are far smaller).
+ * Loading also builds a second form, walked by large pools, in which every
+ * threshold is replaced by its rank among its feature's thresholds (where it
+ * pays, and memory allows; the results are the same).
  */
 typedef struct {
   int32_t num_trees;

@@ -57,7 +57,9 @@ ml2_status ml2_probe_valu(int32_t iters, int32_t blocks, double *ms, double *lan
  * ml2_score_perf and ml2_explorer_round call, on any thread, takes the
  * nonzero fields in place of the planner's choice where the forced shape
  * fits the ensemble and the LDS (a field that does not fit is ignored, as
- * is a zero field).  All zeros restore the planner.  The results of every
+ * is a zero field), and then the float walks run whatever the pool's size
+ * (the walks over threshold codes have no overrides).  All zeros restore the
+ * planner.  The results of every
  * call are unchanged (bit for bit): only the launch shape differs.
  *   split: lanes per candidate (1 or 2)      group: trees per lane (1..16)
  *   waves: waves per workgroup (1..8)        nbuf: LDS chunk buffers (1 or 2)
