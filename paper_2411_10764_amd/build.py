@@ -15,7 +15,8 @@ CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libml2.so")
 SOURCES = ["ml2_host.hip", "walk_kernels.hip", "rank_host.hip", "rank_validity.hip",
-           "rank_perf.hip", "rank_ragged.hip", "topk_kernels.hip", "probe_kernels.hip", "pack.cpp", "rank_pack.cpp"]
+           "rank_perf.hip", "rank_ragged.hip", "topk_kernels.hip", "probe_kernels.hip", "pack.cpp",
+           "rank_pack.cpp", "rank_plan.cpp"]
 ARCH = os.environ.get("ML2_OFFLOAD_ARCH", "gfx950")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -9,10 +9,10 @@
 
 #include "layout.h"
 #include "ml2.h"
+#include "rank_plan.h"
 
 namespace ml2 {
 
-constexpr size_t kLdsBudget = 160 * 1024 - 256;  // LDS of a walk workgroup (static LDS headroom)
 constexpr size_t kTreeSlack = 128 * 1024;  // readable zero bytes after the tree table
 
 // hipFuncSetAttribute(MaxDynamicSharedMemorySize) for kernel fn on the current
@@ -24,9 +24,10 @@ hipError_t ensure_dynamic_lds(const void *fn, size_t bytes);
 // The rank form of an ensemble (rank_pack.h) on the device;
 // ok = 0: the ensemble has none, or ranking a row costs more than it saves.
 struct RankForm {
-  int32_t ok, mode, depth, group, waves, per_cu;  // waves of a workgroup, workgroups of a CU
+  int32_t ok, mode, depth;
+  RankShape shape;
   int32_t nslots, nchunks, nlines;
-  uint32_t slot_bytes, tile_bytes;
+  uint32_t tile_bytes;
   void *block;  // one allocation holding every table below
   const void *slots, *grid, *line_group, *groups, *group_slot, *chunks;
 };

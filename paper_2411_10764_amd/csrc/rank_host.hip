@@ -10,94 +10,6 @@
 namespace ml2 {
 namespace {
 
-constexpr uint32_t kMaxSlot = 64 * 1024;
-
-// The register class of a kernel that shares a CU with `total` waves in all.
-int wave_class(int total) { return total > 16 ? 24 : total > 12 ? 16 : total > 8 ? 12 : total > 4 ? 8 : 4; }
-
-// Bytes that the staging registers of `waves` waves of a class hold.
-size_t stage_bytes(int cls, int waves) {
-  return (size_t)rank_stage_regs(cls) * 16 * rank::kLanes * waves;
-}
-
-size_t queue_bytes(int waves) { return (size_t)waves * 2 * rank::kLanes * sizeof(int32_t); }
-
-// Waves per workgroup, workgroups per CU, trees per lane and slot size for
-// tiles of `tile` bytes per wave and trees of depth D.  Two workgroups of
-// eight waves first: one walks while the other waits at a barrier or for its
-// rows (16M x 128 validity 7.20 -> 6.76 ms against one of sixteen).  They need
-// room for a slot of two groups of trees each, or of 32 KiB (a shorter one
-// spends the gain on restaging: 4M x 96, depth 8, 24 KiB slots: 3.83 ms, one
-// workgroup of sixteen waves with 55 KiB: 3.64); else one workgroup of as many
-// waves as leave that room, by fours, as each SIMD takes a fourth (16M x 128
-// performance: twelve waves and a 58 KiB slot 14.5 ms, sixteen and 23 KiB
-// 16.7, ten 16.4, eight 16.6).  Last, whatever holds one group.  False where
-// no workgroup does.
-bool shape(uint32_t tile, int D, RankForm *r) {
-  struct Shape {
-    int waves, per_cu;
-  };
-  const Shape shapes[] = {{8, 2}, {16, 1}, {12, 1}, {8, 1}, {7, 1}, {6, 1},
-                          {5, 1}, {4, 1},  {3, 1},  {2, 1}, {1, 1}};
-  const uint32_t RB = rank_tree_bytes(D);
-  for (const bool roomy : {true, false}) {
-    for (const auto &groups : rank::kGroups) {
-      const uint32_t one = (uint32_t)groups[D] * RB;
-      if (one == 0) continue;
-      const uint32_t need = roomy ? std::min<uint32_t>(2 * one, 32 * 1024) : 8 * 1024;
-      for (const Shape &sh : shapes) {
-        const size_t fixed = (size_t)sh.waves * tile + queue_bytes(sh.waves);
-        const size_t lds = kLdsBudget / sh.per_cu;
-        if (fixed >= lds) continue;
-        const uint32_t slot =
-            (uint32_t)std::min({lds - fixed, (size_t)kMaxSlot,
-                                stage_bytes(wave_class(sh.waves * sh.per_cu), sh.waves)}) & ~255u;
-        if (slot < std::max(one, need)) continue;
-        r->waves = sh.waves;
-        r->per_cu = sh.per_cu;
-        r->group = groups[D];
-        r->slot_bytes = slot;
-        return true;
-      }
-    }
-  }
-  return false;
-}
-
-// The same for ragged trees, whose slot is fixed.  The walk is bound by the
-// latency of its chain of reads, so as many waves as fit, two workgroups of
-// twelve first (16M x 128 round, 300 trees of depth up to 14 over 64
-// features: 8 waves per CU 9.2 ms, 12 6.6, 16 5.4, 24 4.6).
-size_t ragged_lds(uint32_t tile, int waves) {
-  // a leaf reads a code within ragged_mask of its lane's column
-  size_t past = kRankRow;
-  while (past < tile) past *= 2;
-  const size_t fixed = kRaggedChunkBytes + (size_t)waves * tile;
-  return std::max(fixed + queue_bytes(waves) + waves * sizeof(int), fixed - tile + kRankRow + past);
-}
-
-uint32_t ragged_mask(uint32_t tile, RankMode mode) {
-  uint32_t past = kRankRow;
-  while (past < tile) past *= 2;
-  return (past - 1) & (mode == kRankByte ? ~0xFCu : ~0xFDu);
-}
-
-bool ragged_shape(uint32_t tile, RankForm *r) {
-  struct Shape {
-    int waves, per_cu;
-  };
-  const Shape shapes[] = {{12, 2}, {16, 1}, {12, 1}, {8, 1}, {4, 1}};  // (four hold any tile)
-  for (const Shape &sh : shapes) {
-    if (ragged_lds(tile, sh.waves) * sh.per_cu > kLdsBudget) continue;
-    r->waves = sh.waves;
-    r->per_cu = sh.per_cu;
-    r->group = 1;
-    r->slot_bytes = kRaggedChunkBytes;
-    return true;
-  }
-  return false;
-}
-
 template <typename T>
 size_t place(size_t *at, const std::vector<T> &v) {
   const size_t o = *at;
@@ -117,7 +29,9 @@ void rank_load(const std::vector<TreeView> &views, const RaggedPack *ragged, For
     if (!rank_codes(views, f->num_features, &codes)) return;
     if (ragged && !rank_ragged_fields(&codes)) return;
     r.tile_bytes = codes.rows * kRankRow;
-    if (!(ragged ? ragged_shape(r.tile_bytes, &r) : shape(r.tile_bytes, D, &r))) return;
+    if (!(ragged ? rank_ragged_shape(r.tile_bytes, &r.shape)
+                 : rank_shape(r.tile_bytes, D, &r.shape)))
+      return;
     // Ranking a row costs about 0.8 of a node visit per search step and one
     // per grid feature; a visit of the rank walk takes about 0.28 of a visit
     // less than one of the float walk, 0.56 where that cannot prefetch its
@@ -139,7 +53,7 @@ void rank_load(const std::vector<TreeView> &views, const RaggedPack *ragged, For
     if ((ragged || D < 9) && saves < 40 * steps + 50 * grids) return;
     RankPack p;
     if (!(ragged ? rank_pack_ragged(*ragged, codes, f->num_features, &p)
-                 : rank_pack(views, codes, f->num_features, D, r.group, r.slot_bytes, &p)))
+                 : rank_pack(views, codes, f->num_features, D, r.shape.group, r.shape.slot_bytes, &p)))
       return;
     size_t bytes = p.bytes + kTreeSlack;  // staging reads whole register sets past a slot
     const size_t o_slots = 0, o_grid = place(&bytes, p.grid),
@@ -205,27 +119,16 @@ bool rank_takes(const Forest &f, int64_t n_work, const WalkPlan &plan, bool perf
   if (!r.ok) return false;
   for (int t : {kTuneSplit, kTuneGroup, kTuneWaves, kTuneNbuf, kTuneChunk})
     if (get_tune(t) != 0) return false;  // the overrides shape the float walks
-  if (n_work >= (int64_t)48 * r.waves * r.per_cu * plan.cus) return true;
+  if (n_work >= (int64_t)48 * r.shape.waves * r.shape.per_cu * plan.cus) return true;
   return perf && !f.ragged && plan.waves * plan.group <= 8 && n_work >= (int64_t)64 * plan.cus;
 }
 
-namespace {
-
-struct Launch {
-  int grid, cls;
-  size_t lds;
-};
-
-// The launch shape for n rows: as many workgroups as the chip holds or the
-// pool has units of 64 rows, of no more waves than a workgroup has units.
-RankArgs args_for(const Forest &f, const float *X, int64_t n, int64_t ld, int cu_count,
-                  bool perf, Launch *l) {
+// The arguments of a launch over n rows.
+static RankArgs args_for(const Forest &f, const float *X, int64_t n, int64_t ld, int cu_count,
+                         bool perf, RankLaunch *l) {
   const RankForm &r = f.rank;
-  const int64_t units = (n + rank::kLanes - 1) / rank::kLanes;
-  int w = r.waves, per_cu = r.per_cu;
-  if (units <= (int64_t)cu_count * 8) per_cu = 1;
-  for (int less : {12, 8, 4})
-    if (less < w && units <= (int64_t)cu_count * per_cu * less) w = less;
+  *l = rank_launch(r.shape, r.tile_bytes, f.ragged != 0, (n + rank::kLanes - 1) / rank::kLanes,
+                   cu_count, perf);
   RankArgs a{};
   a.X = X;
   a.n = n;
@@ -240,58 +143,43 @@ RankArgs args_for(const Forest &f, const float *X, int64_t n, int64_t ld, int cu
   a.nchunks = r.nchunks;
   a.nlines = r.nlines;
   a.F = f.num_features;
-  a.slot_bytes = r.slot_bytes;
+  a.slot_bytes = r.shape.slot_bytes;
   a.tile_bytes = r.tile_bytes;
-  a.nthreads = w * rank::kLanes;
+  a.nthreads = l->waves * rank::kLanes;
   a.vec4 = ((reinterpret_cast<uintptr_t>(X) & 15u) == 0 && (ld & 3) == 0 &&
             (f.num_features & 3) == 0)
                ? 1
                : 0;
   a.base = f.base;
   a.missing = r.mode == kRankByte ? kRankRaggedByte : kRankRaggedHalf;
-  a.off_mask = ragged_mask(r.tile_bytes, (RankMode)r.mode);
-  l->lds = f.ragged ? ragged_lds(r.tile_bytes, w)
-                    : (size_t)w * r.tile_bytes + r.slot_bytes + (perf ? queue_bytes(w) : 0);
-  l->cls = wave_class(w * per_cu);
-  l->grid = (int)std::max<int64_t>(1, std::min<int64_t>(units, (int64_t)cu_count * per_cu));
+  a.off_mask = rank_ragged_mask(r.tile_bytes, (RankMode)r.mode);
   return a;
-}
-
-}  // namespace
-
-// A slot must fit the staging registers of the launch, or its end would stay
-// unwritten.
-static bool stages_slot(const Forest &f, const RankArgs &a, const Launch &l) {
-  const int regs = f.ragged ? rank_ragged_stage_regs(l.cls) : rank_stage_regs(l.cls);
-  return (size_t)regs * 16 * a.nthreads >= a.slot_bytes && l.lds <= kLdsBudget;
 }
 
 hipError_t launch_rank_validity(const Forest &f, const float *X, int64_t n, int64_t ld,
                                 uint8_t *valid_out, float *margin_out, int cu_count,
                                 hipStream_t s) {
-  Launch l{};
+  RankLaunch l{};
   RankArgs a = args_for(f, X, n, ld, cu_count, false, &l);
-  if (!stages_slot(f, a, l)) return hipErrorInvalidValue;
+  if (!rank_stages_slot(f.rank.shape, f.ragged != 0, l)) return hipErrorInvalidValue;
   a.valid_out = valid_out;
   a.margin_out = margin_out;
   if (f.ragged)
     return launch_rank_ragged_kernel(false, (RankMode)f.rank.mode, l.cls, a, l.grid, l.lds, s);
-  return launch_rank_validity_kernel(f.rank.depth, (RankMode)f.rank.mode, f.rank.group,
-                                     l.cls, a, l.grid, l.lds, s);
+  return launch_rank_validity_kernel(f.rank.depth, (RankMode)f.rank.mode, l.cls, a, l.grid, l.lds, s);
 }
 
 hipError_t launch_rank_perf(const Forest &f, const float *X, int64_t n, int64_t ld,
                             const uint8_t *valid, float *score_out, int cu_count,
                             hipStream_t s) {
-  Launch l{};
+  RankLaunch l{};
   RankArgs a = args_for(f, X, n, ld, cu_count, true, &l);
-  if (!stages_slot(f, a, l)) return hipErrorInvalidValue;
+  if (!rank_stages_slot(f.rank.shape, f.ragged != 0, l)) return hipErrorInvalidValue;
   a.valid_in = valid;
   a.score_out = score_out;
   if (f.ragged)
     return launch_rank_ragged_kernel(true, (RankMode)f.rank.mode, l.cls, a, l.grid, l.lds, s);
-  return launch_rank_perf_kernel(f.rank.depth, (RankMode)f.rank.mode, f.rank.group,
-                                 l.cls, a, l.grid, l.lds, s);
+  return launch_rank_perf_kernel(f.rank.depth, (RankMode)f.rank.mode, l.cls, a, l.grid, l.lds, s);
 }
 
 }  // namespace ml2

@@ -3,9 +3,9 @@
 
 namespace ml2 {
 
-hipError_t launch_rank_perf_kernel(int depth, RankMode mode, int group, int waves, const RankArgs &a,
+hipError_t launch_rank_perf_kernel(int depth, RankMode mode, int waves, const RankArgs &a,
                                    int grid, size_t lds, hipStream_t s) {
-  return rank::launch<true>(depth, mode, group, waves, a, grid, lds, s);
+  return rank::launch<true>(depth, mode, waves, a, grid, lds, s);
 }
 
 }  // namespace ml2

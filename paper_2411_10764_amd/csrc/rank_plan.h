@@ -1,0 +1,52 @@
+// Launch shapes of the rank walks (rank_pack.h): waves, workgroups per CU,
+// slots and LDS.  Plain C++17 (no HIP), so that it also builds on its own for
+// the CPU tests.
+#pragma once
+
+#include <stddef.h>
+#include <stdint.h>
+
+#include "rank_pack.h"
+
+namespace ml2 {
+
+constexpr size_t kLdsBudget = 160 * 1024 - 256;  // LDS of a walk workgroup (static LDS headroom)
+
+// Registers (16 bytes each) per thread that stage one slot of at most 64 KiB.
+constexpr int rank_stage_regs(int waves) { return (64 + waves - 1) / waves; }
+// The same for a 24 KiB slot of ragged trees and the smallest workgroup of a
+// class: of 24 waves that share a CU twelve, of 16 eight, of 12 twelve, of 8
+// and of 4 four.
+constexpr int rank_ragged_stage_regs(int waves) {
+  return waves == 24 || waves == 12 ? 2 : waves == 16 ? 3 : 6;
+}
+
+// Trees walked together by a lane, per depth.
+constexpr int kRankGroup[kRankMaxDepth + 1] = {0, 0, 0, 0, 8, 8, 8, 8, 8, 4, 4, 2, 1};
+
+// Waves of a workgroup, workgroups of a CU, trees per lane and slot size.
+struct RankShape {
+  int32_t waves, per_cu, group;
+  uint32_t slot_bytes;
+};
+// For tiles of `tile` bytes per wave and perfect trees of depth D, or ragged
+// trees; false where no workgroup fits.
+bool rank_shape(uint32_t tile, int D, RankShape *out);
+bool rank_ragged_shape(uint32_t tile, RankShape *out);
+
+// One launch over `units` units of 64 rows.
+struct RankLaunch {
+  int32_t waves, per_cu, grid;
+  int32_t cls;  // register class: the most waves that share a CU
+  size_t lds;
+};
+RankLaunch rank_launch(const RankShape &shape, uint32_t tile, bool ragged, int64_t units,
+                       int cu_count, bool perf);
+// Whether a launch's staging registers hold a slot and its LDS fits (else the
+// slot's end would stay unwritten).
+bool rank_stages_slot(const RankShape &shape, bool ragged, const RankLaunch &l);
+
+// Ragged trees: the bits of a code's offset in the tile.
+uint32_t rank_ragged_mask(uint32_t tile, RankMode mode);
+
+}  // namespace ml2

@@ -3,9 +3,9 @@
 
 namespace ml2 {
 
-hipError_t launch_rank_validity_kernel(int depth, RankMode mode, int group, int waves,
-                                       const RankArgs &a, int grid, size_t lds, hipStream_t s) {
-  return rank::launch<false>(depth, mode, group, waves, a, grid, lds, s);
+hipError_t launch_rank_validity_kernel(int depth, RankMode mode, int waves, const RankArgs &a,
+                                       int grid, size_t lds, hipStream_t s) {
+  return rank::launch<false>(depth, mode, waves, a, grid, lds, s);
 }
 
 }  // namespace ml2

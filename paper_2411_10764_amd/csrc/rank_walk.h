@@ -57,16 +57,6 @@ struct RankArgs {
   float *score_out;
 };
 
-// Registers (16 bytes each) per thread that stage one slot of at most 64 KiB.
-constexpr int rank_stage_regs(int waves) { return (64 + waves - 1) / waves; }
-// The same for a 24 KiB slot of ragged trees and the smallest workgroup of a
-// class: of 24 waves that share a CU twelve, of 16 eight, of 12 twelve, of 8
-// and of 4 four.
-constexpr int rank_ragged_stage_regs(int waves) {
-  return waves == 24 || waves == 12 ? 2 : waves == 16 ? 3 : 6;
-}
-
-
 namespace rank {
 
 constexpr int kLanes = 64;
@@ -585,10 +575,6 @@ rank_kernel(RankArgs a) {
                       });
 }
 
-// Trees walked together by a lane, per depth.
-constexpr int kGroups[2][13] = {{0, 0, 0, 0, 8, 8, 8, 8, 8, 4, 4, 2, 1},
-                                {0, 0, 0, 0, 0, 0, 0, 0, 4, 0, 2, 1, 0}};
-
 template <int D, int G, RankMode M, int W, bool PERF>
 hipError_t launch_one(const RankArgs &a, int grid, size_t lds, hipStream_t s) {
   const void *fn = reinterpret_cast<const void *>(&rank_kernel<D, G, M, W, PERF>);
@@ -606,9 +592,10 @@ hipError_t launch_waves(int waves, const RankArgs &a, int grid, size_t lds, hipS
   return launch_one<D, G, M, 4, PERF>(a, grid, lds, s);
 }
 
-template <int D, int G, bool PERF>
-hipError_t launch_group(RankMode mode, int waves, const RankArgs &a, int grid, size_t lds,
+template <int D, bool PERF>
+hipError_t launch_depth(RankMode mode, int waves, const RankArgs &a, int grid, size_t lds,
                         hipStream_t s) {
+  constexpr int G = kRankGroup[D];
   switch (mode) {
     case kRankByte: return launch_waves<D, G, kRankByte, PERF>(waves, a, grid, lds, s);
     case kRankHalf: return launch_waves<D, G, kRankHalf, PERF>(waves, a, grid, lds, s);
@@ -616,31 +603,19 @@ hipError_t launch_group(RankMode mode, int waves, const RankArgs &a, int grid, s
   }
 }
 
-template <int D, bool PERF>
-hipError_t launch_depth(RankMode mode, int group, int waves, const RankArgs &a, int grid,
-                        size_t lds, hipStream_t s) {
-  if (group == kGroups[0][D])
-    return launch_group<D, kGroups[0][D], PERF>(mode, waves, a, grid, lds, s);
-  if constexpr (kGroups[1][D] != 0) {
-    if (group == kGroups[1][D])
-      return launch_group<D, kGroups[1][D], PERF>(mode, waves, a, grid, lds, s);
-  }
-  return hipErrorInvalidValue;
-}
-
 template <bool PERF>
-hipError_t launch(int depth, RankMode mode, int group, int waves, const RankArgs &a, int grid,
-                  size_t lds, hipStream_t s) {
+hipError_t launch(int depth, RankMode mode, int waves, const RankArgs &a, int grid, size_t lds,
+                  hipStream_t s) {
   switch (depth) {
-    case 4: return launch_depth<4, PERF>(mode, group, waves, a, grid, lds, s);
-    case 5: return launch_depth<5, PERF>(mode, group, waves, a, grid, lds, s);
-    case 6: return launch_depth<6, PERF>(mode, group, waves, a, grid, lds, s);
-    case 7: return launch_depth<7, PERF>(mode, group, waves, a, grid, lds, s);
-    case 8: return launch_depth<8, PERF>(mode, group, waves, a, grid, lds, s);
-    case 9: return launch_depth<9, PERF>(mode, group, waves, a, grid, lds, s);
-    case 10: return launch_depth<10, PERF>(mode, group, waves, a, grid, lds, s);
-    case 11: return launch_depth<11, PERF>(mode, group, waves, a, grid, lds, s);
-    case 12: return launch_depth<12, PERF>(mode, group, waves, a, grid, lds, s);
+    case 4: return launch_depth<4, PERF>(mode, waves, a, grid, lds, s);
+    case 5: return launch_depth<5, PERF>(mode, waves, a, grid, lds, s);
+    case 6: return launch_depth<6, PERF>(mode, waves, a, grid, lds, s);
+    case 7: return launch_depth<7, PERF>(mode, waves, a, grid, lds, s);
+    case 8: return launch_depth<8, PERF>(mode, waves, a, grid, lds, s);
+    case 9: return launch_depth<9, PERF>(mode, waves, a, grid, lds, s);
+    case 10: return launch_depth<10, PERF>(mode, waves, a, grid, lds, s);
+    case 11: return launch_depth<11, PERF>(mode, waves, a, grid, lds, s);
+    case 12: return launch_depth<12, PERF>(mode, waves, a, grid, lds, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -649,9 +624,9 @@ hipError_t launch(int depth, RankMode mode, int group, int waves, const RankArgs
 
 hipError_t launch_rank_ragged_kernel(bool perf, RankMode mode, int waves, const RankArgs &a,
                                      int grid, size_t lds, hipStream_t s);
-hipError_t launch_rank_validity_kernel(int depth, RankMode mode, int group, int waves,
-                                       const RankArgs &a, int grid, size_t lds, hipStream_t s);
-hipError_t launch_rank_perf_kernel(int depth, RankMode mode, int group, int waves, const RankArgs &a,
+hipError_t launch_rank_validity_kernel(int depth, RankMode mode, int waves, const RankArgs &a,
+                                       int grid, size_t lds, hipStream_t s);
+hipError_t launch_rank_perf_kernel(int depth, RankMode mode, int waves, const RankArgs &a,
                                    int grid, size_t lds, hipStream_t s);
 
 }  // namespace ml2

@@ -1646,6 +1646,7 @@ hipError_t launch_leaves_depth(const WalkArgs &a, int G, size_t lds, int row_til
   return hipErrorInvalidValue;
 }
 
+// (depths 10 to 12: leaves_gather_kernel)
 hipError_t launch_leaves(int depth, const WalkArgs &a, int G, size_t lds, int row_tiles,
                          hipStream_t s) {
   switch (depth) {
@@ -1659,9 +1660,6 @@ hipError_t launch_leaves(int depth, const WalkArgs &a, int G, size_t lds, int ro
     case 7: return launch_leaves_depth<7>(a, G, lds, row_tiles, s);
     case 8: return launch_leaves_depth<8>(a, G, lds, row_tiles, s);
     case 9: return launch_leaves_depth<9>(a, G, lds, row_tiles, s);
-    case 10: return launch_leaves_depth<10>(a, G, lds, row_tiles, s);
-    case 11: return launch_leaves_depth<11>(a, G, lds, row_tiles, s);
-    case 12: return launch_leaves_depth<12>(a, G, lds, row_tiles, s);
     default: return hipErrorInvalidValue;
   }
 }

@@ -19,21 +19,31 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(os.path.dirname(HERE), "paper_2411_10764_amd", "csrc")
 
 
-def test_rank_form_walks_to_the_same_leaves(tmp_path):
+def _run_driver(tmp_path, name, sources):
     gxx = shutil.which("g++")
     if gxx is None:
         pytest.skip("g++ not available")
-    exe = str(tmp_path / "rank_check_driver")
+    exe = str(tmp_path / name)
     r = subprocess.run([gxx, "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined",
                         "-fno-sanitize-recover=all", "-ffp-contract=off", "-Wall", "-Werror",
-                        "-I", CSRC, os.path.join(HERE, "rank_check_driver.cpp"),
-                        os.path.join(CSRC, "rank_pack.cpp"), os.path.join(CSRC, "pack.cpp"),
-                        "-pthread", "-o", exe],
+                        "-I", CSRC, os.path.join(HERE, name + ".cpp"),
+                        *(os.path.join(CSRC, s) for s in sources), "-pthread", "-o", exe],
                        capture_output=True, text=True)
     assert r.returncode == 0, r.stdout + r.stderr
     r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout + r.stderr
-    lines = r.stdout.splitlines()
-    assert len(lines) == 23 and all(line.startswith("ok ") for line in lines), r.stdout
+    return r.stdout
+
+
+def test_rank_form_walks_to_the_same_leaves(tmp_path):
+    out = _run_driver(tmp_path, "rank_check_driver", ["rank_pack.cpp", "pack.cpp"])
+    lines = out.splitlines()
+    assert len(lines) == 23 and all(line.startswith("ok ") for line in lines), out
     for mode in ("byte", "half", "packed", "ragged byte", "ragged half"):
-        assert any(f", {mode}, " in line for line in lines), r.stdout
+        assert any(f", {mode}, " in line for line in lines), out
+
+
+def test_every_tile_and_depth_has_a_launch_shape(tmp_path):
+    """rank_plan.cpp: a shape for every tile and depth, and launches that stage
+    whole slots within the LDS (tests/rank_plan_driver.cpp)."""
+    assert _run_driver(tmp_path, "rank_plan_driver", ["rank_plan.cpp"]).strip() == "ok"
