@@ -118,15 +118,17 @@ ml2_status current_device(int *dev) {
 
 // ---- descriptor validation ------------------------------------------------
 
-// Checks that tree t is a proper binary tree rooted at 0 and returns its depth.
+// Checks that tree t is a proper binary tree rooted at 0 and returns its depth
+// and the nodes on a walk whose every split goes either way equally often.
 ml2_status check_tree(const ml2_ensemble_desc &d, int32_t t, const TreeView &tv, int *depth_out,
-                      double *max_abs_leaf) {
+                      double *max_abs_leaf, double *path) {
   std::vector<uint8_t> seen((size_t)tv.size, 0);
   std::vector<std::pair<int32_t, int>> stack;
   stack.emplace_back(0, 0);
   seen[0] = 1;
   int64_t visited = 1;
   int depth = 0;
+  *path = 0.0;
   while (!stack.empty()) {
     const auto [node, lvl] = stack.back();
     stack.pop_back();
@@ -137,6 +139,7 @@ ml2_status check_tree(const ml2_ensemble_desc &d, int32_t t, const TreeView &tv,
         return fail(ML2_ERR_INVALID_ARG, "tree %d node %d: leaf value is not finite", t, node);
       if (fabs((double)v) > *max_abs_leaf) *max_abs_leaf = fabs((double)v);
       if (lvl > depth) depth = lvl;
+      *path += ldexp(lvl + 1.0, -lvl);
       continue;
     }
     if (l < 0 || r < 0 || l >= tv.size || r >= tv.size)
@@ -271,7 +274,7 @@ ml2_status ml2_load_ensemble(const ml2_ensemble_desc *desc, ml2_ensemble **out) 
     return fail(ML2_ERR_INVALID_ARG, "tree_node_offset[0] = %lld, expected 0",
                 (long long)d.tree_node_offset[0]);
   int depth = 1;
-  double max_leaf = 0.0;
+  double max_leaf = 0.0, path = 0.0;
   int64_t total_nodes = 0, max_nodes = 0;
   bool any_default_left = false;
   std::vector<TreeView> views((size_t)d.num_trees);
@@ -279,7 +282,7 @@ ml2_status ml2_load_ensemble(const ml2_ensemble_desc *desc, ml2_ensemble **out) 
   // Trees are checked side by side; the first bad one is then checked again
   // here for its message.
   const int64_t T = d.num_trees;
-  std::vector<double> leaf_of((size_t)T, 0.0);
+  std::vector<double> leaf_of((size_t)T, 0.0), path_of((size_t)T, 0.0);
   std::vector<uint8_t> bad((size_t)T, 0);
   int64_t ranged = 0;  // trees before the first bad node range
   for (; ranged < T; ++ranged) {
@@ -294,7 +297,7 @@ ml2_status ml2_load_ensemble(const ml2_ensemble_desc *desc, ml2_ensemble **out) 
   try {
     ml2::parallel_for(ranged, ranged ? d.tree_node_offset[ranged] : 0, [&](int64_t t) {
       bad[(size_t)t] = check_tree(d, (int32_t)t, views[(size_t)t], &depths[(size_t)t],
-                                  &leaf_of[(size_t)t]) != ML2_OK;
+                                  &leaf_of[(size_t)t], &path_of[(size_t)t]) != ML2_OK;
     });
   } catch (const std::bad_alloc &) {
     return fail(ML2_ERR_OUT_OF_MEMORY, "host memory for checking the trees");
@@ -305,9 +308,10 @@ ml2_status ml2_load_ensemble(const ml2_ensemble_desc *desc, ml2_ensemble **out) 
                   t, (long long)d.tree_node_offset[t], (long long)d.tree_node_offset[t + 1]);
     const TreeView &tv = views[(size_t)t];
     if (bad[(size_t)t])
-      return check_tree(d, t, tv, &depths[(size_t)t], &leaf_of[(size_t)t]);
+      return check_tree(d, t, tv, &depths[(size_t)t], &leaf_of[(size_t)t], &path_of[(size_t)t]);
     depth = std::max(depth, depths[(size_t)t]);
     max_leaf = std::max(max_leaf, leaf_of[(size_t)t]);
+    path += path_of[(size_t)t];
     total_nodes += tv.size;
     if (tv.size > max_nodes) max_nodes = tv.size;
     if (tv.dl)
@@ -390,7 +394,7 @@ ml2_status ml2_load_ensemble(const ml2_ensemble_desc *desc, ml2_ensemble **out) 
     (void)hipFree(f.d_trees);
     return hip_fail(e, "hipMemcpy");
   }
-  ml2::rank_load(views, ragged ? &pk : nullptr, &f);
+  ml2::rank_load(views, ragged ? &pk : nullptr, path, cu_count(f.device), &f);
   ml2_ensemble *h = new (std::nothrow) ml2_ensemble;
   if (!h) {
     ml2::rank_free(&f);

@@ -28,6 +28,7 @@ struct RankForm {
   RankShape shape;
   int32_t nslots, nchunks, nlines;
   uint32_t tile_bytes;
+  WalkWork work;
   void *block;  // one allocation holding every table below
   const void *slots, *grid, *line_group, *groups, *group_slot, *chunks;
 };
@@ -60,9 +61,10 @@ struct WalkPlan {
 };
 
 // Returns false (and sets *why) if no plan fits the LDS of one workgroup.
-// survivors: the walk covers the rows a mask accepts out of n_work.
+// survivors: the walk covers the rows a mask accepts out of n_work; tuned: the
+// tuning overrides apply.
 bool plan_walk(const Forest &f, int64_t n_work, int cu_count, WalkPlan *plan, const char **why,
-               bool survivors = false);
+               bool survivors = false, bool tuned = true);
 
 // Validity and performance in one pass over the pool (fused_kernel): false
 // where the two ensembles or the pool do not allow it.  nv, np: records of V
@@ -79,11 +81,14 @@ hipError_t launch_fused(const Forest &v, const Forest &p, const WalkPlan &pl, in
 // memory) f->rank.ok stays 0 and the float walks take every call.
 struct TreeView;
 struct RaggedPack;
-void rank_load(const std::vector<TreeView> &views, const RaggedPack *ragged, Forest *f);
+// path: nodes on a row's walks in all trees, leaves included.
+void rank_load(const std::vector<TreeView> &views, const RaggedPack *ragged, double path,
+               int cu_count, Forest *f);
 void rank_free(Forest *f);
-// Whether a walk of n_work rows (perf: the performance walk) takes the rank
+// Whether a walk over n rows of X (perf: the performance walk) takes the rank
 // form rather than the float walk of `plan`.
-bool rank_takes(const Forest &f, int64_t n_work, const WalkPlan &plan, bool perf);
+bool rank_takes(const Forest &f, const float *X, int64_t n, int64_t ld, const WalkPlan &plan,
+                bool perf);
 hipError_t launch_rank_validity(const Forest &f, const float *X, int64_t n, int64_t ld,
                                 uint8_t *valid_out, float *margin_out, int cu_count,
                                 hipStream_t s);

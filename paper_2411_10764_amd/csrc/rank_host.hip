@@ -17,9 +17,68 @@ size_t place(size_t *at, const std::vector<T> &v) {
   return o;
 }
 
+FloatShape float_shape(const WalkPlan &p) {
+  return FloatShape{p.split, p.waves, p.group, p.chunk_trees, p.grid};
+}
+
+WalkWork work_of(const std::vector<TreeView> &views, const RankCodes &codes, const Forest &f,
+                 const RankShape &shape, double path) {
+  WalkWork w{};
+  w.ragged = f.ragged;
+  w.features = f.num_features;
+  w.depth = f.depth;
+  w.records = f.records;
+  w.trees = (int32_t)views.size();
+  w.path = path;
+  size_t tables = 0;
+  for (int32_t c = 0; c < f.num_features; ++c) {
+    int32_t steps = 0;
+    for (size_t n = codes.table[(size_t)c].size(); n; n >>= 1) ++steps;
+    w.steps += steps;
+    tables += steps ? (size_t)4 << steps : 0;
+    w.grids += codes.grid[(size_t)c].top != 0.0f;
+  }
+  const size_t trees = f.ragged ? (size_t)f.records * shape.slot_bytes
+                                : views.size() * rank_tree_bytes(f.depth);
+  w.slots = (int32_t)((tables + trees + shape.slot_bytes - 1) / shape.slot_bytes);
+  return w;
+}
+
+// Ensembles that are small beside the searches of a row keep the float form
+// alone: what ranking gains is little or nothing (412,590 x 136, 42 trees of
+// depth 4: 53 us against 109; 427,763 x 96, 190 of depth 6: 149 against 155;
+// 16M x 128, 300 of depth 6: 7.84 ms against 7.0), and loading a second form
+// takes longer than that.  In node visits per row, a visit saves 0.28 (0.56
+// where the float walk cannot prefetch its rows), a ragged tree 9, and ranking
+// costs 0.8 per search step and 1 per grid feature.  Trees of depth 9
+// and above leave the float walk few trees per lane or few waves, and are
+// never small (500,000 x 256, 100 of depth 12: 47.3 ms against 1.3).
+bool small(const WalkWork &w) {
+  if (!w.ragged && w.depth >= 9) return false;
+  const bool prefetched = row_kind(true, w.features) == kRowsAhead;
+  const int64_t saves = w.ragged ? 450 * (int64_t)w.trees
+                                 : (prefetched ? 14 : 28) * (int64_t)w.trees * w.depth;
+  return saves < 40 * (int64_t)w.steps + 50 * (int64_t)w.grids;
+}
+
+// Whether the estimates save at least 50 us of a walk over 16 million rows side
+// by side (ld = F): few deep trees over many features and ragged trees of one
+// or two splits do not (1 million rows, 10 trees of depth 9 over 128 features
+// 152 us against 209; 20 ragged stumps 168 against 390 at 1.5 million).
+bool ever_pays(const Forest &f, const RankForm &r, int cu_count) {
+  const int64_t n = (int64_t)1 << 24;
+  WalkPlan p;
+  const char *why = nullptr;
+  if (!plan_walk(f, n, cu_count, &p, &why, false, false)) return false;
+  const RowKind kind = row_kind(f.num_features % 4 == 0, f.num_features);
+  return rank_walk_us(r.work, r.shape, kind, (double)n, cu_count) + 50.0 <
+         float_walk_us(r.work, float_shape(p), kind, (double)n, cu_count);
+}
+
 }  // namespace
 
-void rank_load(const std::vector<TreeView> &views, const RaggedPack *ragged, Forest *f) {
+void rank_load(const std::vector<TreeView> &views, const RaggedPack *ragged, double path,
+               int cu_count, Forest *f) {
   RankForm r{};
   f->rank = r;
   const int D = f->depth;
@@ -32,25 +91,8 @@ void rank_load(const std::vector<TreeView> &views, const RaggedPack *ragged, For
     if (!(ragged ? rank_ragged_shape(r.tile_bytes, &r.shape)
                  : rank_shape(r.tile_bytes, D, &r.shape)))
       return;
-    // Ranking a row costs about 0.8 of a node visit per search step and one
-    // per grid feature; a visit of the rank walk takes about 0.28 of a visit
-    // less than one of the float walk, 0.56 where that cannot prefetch its
-    // rows, and a ragged tree about nine visits less.  So small ensembles over
-    // many features keep the float walks (412,590 x 136, 42 trees of depth 4:
-    // 53 us against 109; 427,763 x 96, 190 of depth 6: 149 against 155; 16M x
-    // 128, 300 of depth 6: 7.84 ms against 7.0).  Trees of depth 9 and above
-    // leave those few trees per lane or few waves, and always rank (262,144 x
-    // 96, 100 trees of depth 10: 193 us against 101; 500,000 x 256, 100 of
-    // depth 12: 47.3 ms against 1.3).
-    int64_t steps = 0, grids = 0;  // of ranking one row
-    for (int32_t c = 0; c < f->num_features; ++c) {
-      for (size_t n = codes.table[(size_t)c].size(); n; n >>= 1) ++steps;
-      grids += codes.grid[(size_t)c].top != 0.0f;
-    }
-    const bool prefetched = f->num_features <= 128 && f->num_features % 4 == 0;
-    const int64_t saves = ragged ? 450 * (int64_t)f->num_trees
-                                 : (prefetched ? 14 : 28) * (int64_t)f->num_trees * D;
-    if ((ragged || D < 9) && saves < 40 * steps + 50 * grids) return;
+    r.work = work_of(views, codes, *f, r.shape, path);
+    if (small(r.work) || !ever_pays(*f, r, cu_count)) return;
     RankPack p;
     if (!(ragged ? rank_pack_ragged(*ragged, codes, f->num_features, &p)
                  : rank_pack(views, codes, f->num_features, D, r.shape.group, r.shape.slot_bytes, &p)))
@@ -103,24 +145,30 @@ void rank_free(Forest *f) {
   f->rank = RankForm{};
 }
 
-// From three quarters of a round of every CU on (196,608 rows with 16 waves a
-// CU) a walk ranks where that pays.  Below, a walk takes as long as its
-// longest lane, and the float walk's two lanes per candidate and shorter
-// start win: validity, 300 trees of depth 6 over 128 features, 65,536 rows 38
-// us against 84, 262,144 rows 129 against 132, 16M rows 7.84 ms against 7.0;
-// performance, 177 trees of depth 7 over 76, 4,320 rows 28 us against 58.
-// Not so where the float walk's plan holds at most eight walks per lane column
-// (waves times trees per lane) and the pool has some rows per CU: 644 trees of
-// depth 10 over 112 features, 167,534 rows 1,040 us against 400; 499 over 159,
-// 54,335 rows 984 against 313; but 681 over 112 and 2,173 rows 362 against
-// 394.
-bool rank_takes(const Forest &f, int64_t n_work, const WalkPlan &plan, bool perf) {
+// A walk ranks where the estimates say that it is the faster one, from three
+// quarters of a round of every CU on (196,608 rows with 16 waves a CU): below,
+// a walk takes as long as its longest lane, and the float walk's two lanes per
+// candidate and shorter start win (validity, 300 trees of depth 6 over 128
+// features, 65,536 rows 38 us against 84; performance, 177 trees of depth 7
+// over 76, 4,320 rows 28 us against 58).  Not so where the float walk's plan
+// holds at most eight walks per lane column (waves times trees per lane) and
+// the pool has some rows per CU: 644 trees of depth 10 over 112 features,
+// 167,534 rows 1,040 us against 400; 499 over 159, 54,335 rows 984 against
+// 313; but 681 over 112 and 2,173 rows 362 against 394.
+bool rank_takes(const Forest &f, const float *X, int64_t n, int64_t ld, const WalkPlan &plan,
+                bool perf) {
   const RankForm &r = f.rank;
   if (!r.ok) return false;
   for (int t : {kTuneSplit, kTuneGroup, kTuneWaves, kTuneNbuf, kTuneChunk})
     if (get_tune(t) != 0) return false;  // the overrides shape the float walks
-  if (n_work >= (int64_t)48 * r.shape.waves * r.shape.per_cu * plan.cus) return true;
-  return perf && !f.ragged && plan.waves * plan.group <= 8 && n_work >= (int64_t)64 * plan.cus;
+  const bool round = n >= (int64_t)48 * r.shape.waves * r.shape.per_cu * plan.cus;
+  const bool few_walks =
+      perf && !f.ragged && plan.waves * plan.group <= 8 && n >= (int64_t)64 * plan.cus;
+  if (!round && !few_walks) return false;
+  const bool aligned = (reinterpret_cast<uintptr_t>(X) & 15u) == 0 && (ld & 3) == 0;
+  const RowKind kind = row_kind(aligned, f.num_features);
+  return rank_walk_us(r.work, r.shape, kind, (double)n, plan.cus) <
+         float_walk_us(r.work, float_shape(plan), kind, (double)n, plan.cus);
 }
 
 // The arguments of a launch over n rows.

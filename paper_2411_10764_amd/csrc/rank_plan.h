@@ -46,6 +46,29 @@ RankLaunch rank_launch(const RankShape &shape, uint32_t tile, bool ragged, int64
 // slot's end would stay unwritten).
 bool rank_stages_slot(const RankShape &shape, bool ragged, const RankLaunch &l);
 
+// What the walks of an ensemble do, for the two estimates below.
+struct WalkWork {
+  int32_t ragged, features, depth;
+  int32_t records;         // staged by the float walk: trees (padded) or ragged slots
+  int32_t trees, slots;    // of the ensemble; of the rank form, tables included
+  int32_t steps, grids;    // search steps and grid features of ranking a row
+  double path;             // ragged: nodes on a row's walks, leaves included
+};
+// The shape of a float walk: lanes per candidate, waves, trees per lane,
+// records per chunk, workgroups.
+struct FloatShape {
+  int32_t split, waves, group, chunk, grid;
+};
+// How rows lie: loaded as whole 16-byte vectors and a round ahead, as vectors,
+// or a float at a time.
+enum RowKind { kRowsAhead, kRowsVector, kRowsSingle };
+RowKind row_kind(bool aligned, int32_t features);
+
+// Estimated time in microseconds of a walk over `rows` rows.  Which walk takes
+// a call is their comparison, so only their ratio matters.
+double float_walk_us(const WalkWork &w, const FloatShape &s, RowKind kind, double rows, int cus);
+double rank_walk_us(const WalkWork &w, const RankShape &s, RowKind kind, double rows, int cus);
+
 // Ragged trees: the bits of a code's offset in the tile.
 uint32_t rank_ragged_mask(uint32_t tile, RankMode mode);
 

@@ -1895,12 +1895,12 @@ int get_tune(int field) { return g_tune[field].load(std::memory_order_relaxed); 
 // (ml2_tune_walk_plan) replace the choice where they fit; overrides that do
 // not fit are ignored.
 bool plan_walk(const Forest &f, int64_t n_work, int cu_count, WalkPlan *p, const char **why,
-               bool survivors) {
-  const int want_s = get_tune(kTuneSplit);
-  const int want_g = get_tune(kTuneGroup);
-  const int want_w = get_tune(kTuneWaves);
-  const int want_b = get_tune(kTuneNbuf);
-  const int want_c = get_tune(kTuneChunk);
+               bool survivors, bool tuned) {
+  const int want_s = tuned ? get_tune(kTuneSplit) : 0;
+  const int want_g = tuned ? get_tune(kTuneGroup) : 0;
+  const int want_w = tuned ? get_tune(kTuneWaves) : 0;
+  const int want_b = tuned ? get_tune(kTuneNbuf) : 0;
+  const int want_c = tuned ? get_tune(kTuneChunk) : 0;
   const int groups[5] = {16, 8, 4, 2, 1};
   // ragged trees with one lane per candidate: one tree per lane first (each
   // lane then moves to its next tree as soon as its walk is on a leaf, and
@@ -1952,7 +1952,7 @@ bool plan_walk(const Forest &f, int64_t n_work, int cu_count, WalkPlan *p, const
 
 hipError_t launch_validity(const Forest &f, const WalkPlan &p, const float *X, int64_t n,
                            int64_t ld, uint8_t *valid_out, float *margin_out, hipStream_t s) {
-  if (rank_takes(f, n, p, false))
+  if (rank_takes(f, X, n, ld, p, false))
     return launch_rank_validity(f, X, n, ld, valid_out, margin_out, p.cus, s);
   WalkArgs a = make_args(f, p, X, n, ld);
   a.valid_out = valid_out;
@@ -1962,7 +1962,7 @@ hipError_t launch_validity(const Forest &f, const WalkPlan &p, const float *X, i
 
 hipError_t launch_perf(const Forest &f, const WalkPlan &p, const float *X, int64_t n,
                        int64_t ld, const uint8_t *valid, float *score_out, hipStream_t s) {
-  if (rank_takes(f, n, p, true))
+  if (rank_takes(f, X, n, ld, p, true))
     return launch_rank_perf(f, X, n, ld, valid, score_out, p.cus, s);
   WalkArgs a = make_args(f, p, X, n, ld);
   a.valid_in = valid;
