@@ -85,10 +85,11 @@ struct RaggedPack;
 void rank_load(const std::vector<TreeView> &views, const RaggedPack *ragged, double path,
                int cu_count, Forest *f);
 void rank_free(Forest *f);
-// Whether a walk over n rows of X (perf: the performance walk) takes the rank
-// form rather than the float walk of `plan`.
+// Whether a walk over n rows of X (perf: the performance walk; masked: over
+// those that a mask accepts) takes the rank form rather than the float walk of
+// `plan`.
 bool rank_takes(const Forest &f, const float *X, int64_t n, int64_t ld, const WalkPlan &plan,
-                bool perf);
+                bool perf, bool masked);
 hipError_t launch_rank_validity(const Forest &f, const float *X, int64_t n, int64_t ld,
                                 uint8_t *valid_out, float *margin_out, int cu_count,
                                 hipStream_t s);

@@ -68,6 +68,8 @@ RowKind row_kind(bool aligned, int32_t features);
 // a call is their comparison, so only their ratio matters.
 double float_walk_us(const WalkWork &w, const FloatShape &s, RowKind kind, double rows, int cus);
 double rank_walk_us(const WalkWork &w, const RankShape &s, RowKind kind, double rows, int cus);
+// Rows of n at which a walk over the rows that a mask accepts is priced.
+inline double masked_rows(double n) { return 0.15 * n; }
 
 // Ragged trees: the bits of a code's offset in the tile.
 uint32_t rank_ragged_mask(uint32_t tile, RankMode mode);

@@ -1952,7 +1952,7 @@ bool plan_walk(const Forest &f, int64_t n_work, int cu_count, WalkPlan *p, const
 
 hipError_t launch_validity(const Forest &f, const WalkPlan &p, const float *X, int64_t n,
                            int64_t ld, uint8_t *valid_out, float *margin_out, hipStream_t s) {
-  if (rank_takes(f, X, n, ld, p, false))
+  if (rank_takes(f, X, n, ld, p, false, false))
     return launch_rank_validity(f, X, n, ld, valid_out, margin_out, p.cus, s);
   WalkArgs a = make_args(f, p, X, n, ld);
   a.valid_out = valid_out;
@@ -1962,7 +1962,7 @@ hipError_t launch_validity(const Forest &f, const WalkPlan &p, const float *X, i
 
 hipError_t launch_perf(const Forest &f, const WalkPlan &p, const float *X, int64_t n,
                        int64_t ld, const uint8_t *valid, float *score_out, hipStream_t s) {
-  if (rank_takes(f, X, n, ld, p, true))
+  if (rank_takes(f, X, n, ld, p, true, valid != nullptr))
     return launch_rank_perf(f, X, n, ld, valid, score_out, p.cus, s);
   WalkArgs a = make_args(f, p, X, n, ld);
   a.valid_in = valid;

@@ -45,5 +45,6 @@ def test_rank_form_walks_to_the_same_leaves(tmp_path):
 
 def test_every_tile_and_depth_has_a_launch_shape(tmp_path):
     """rank_plan.cpp: a shape for every tile and depth, and launches that stage
-    whole slots within the LDS (tests/rank_plan_driver.cpp)."""
+    whole slots within the LDS; the estimates choose the faster of two measured
+    walks (tests/rank_plan_driver.cpp)."""
     assert _run_driver(tmp_path, "rank_plan_driver", ["rank_plan.cpp"]).strip() == "ok"
