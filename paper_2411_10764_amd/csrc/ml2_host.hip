@@ -128,7 +128,7 @@ ml2_status check_tree(const ml2_ensemble_desc &d, int32_t t, const TreeView &tv,
   seen[0] = 1;
   int64_t visited = 1;
   int depth = 0;
-  *path = 0.0;
+  int32_t leaves[ML2_MAX_DEPTH + 1] = {0};  // per level
   while (!stack.empty()) {
     const auto [node, lvl] = stack.back();
     stack.pop_back();
@@ -139,7 +139,7 @@ ml2_status check_tree(const ml2_ensemble_desc &d, int32_t t, const TreeView &tv,
         return fail(ML2_ERR_INVALID_ARG, "tree %d node %d: leaf value is not finite", t, node);
       if (fabs((double)v) > *max_abs_leaf) *max_abs_leaf = fabs((double)v);
       if (lvl > depth) depth = lvl;
-      *path += ldexp(lvl + 1.0, -lvl);
+      ++leaves[lvl];
       continue;
     }
     if (l < 0 || r < 0 || l >= tv.size || r >= tv.size)
@@ -166,6 +166,8 @@ ml2_status check_tree(const ml2_ensemble_desc &d, int32_t t, const TreeView &tv,
     return fail(ML2_ERR_INVALID_ARG, "tree %d: %lld of %lld nodes unreachable from the root", t,
                 (long long)(tv.size - visited), (long long)tv.size);
   *depth_out = depth;
+  *path = 0.0;
+  for (int l = 0; l <= depth; ++l) *path += ldexp((l + 1.0) * leaves[l], -l);
   return ML2_OK;
 }
 

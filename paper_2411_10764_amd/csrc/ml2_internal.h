@@ -58,6 +58,7 @@ struct WalkPlan {
   size_t lds_bytes; // dynamic LDS per workgroup
   int grid;         // workgroups
   int cus;          // compute units of the device
+  int copied;       // 1: one chunk buffer, filled while the waves wait
 };
 
 // Returns false (and sets *why) if no plan fits the LDS of one workgroup.

@@ -18,7 +18,7 @@ size_t place(size_t *at, const std::vector<T> &v) {
 }
 
 FloatShape float_shape(const WalkPlan &p) {
-  return FloatShape{p.split, p.waves, p.group, p.chunk_trees, p.grid};
+  return FloatShape{p.split, p.waves, p.group, p.chunk_trees, p.grid, p.copied};
 }
 
 WalkWork work_of(const std::vector<TreeView> &views, const RankCodes &codes, const Forest &f,
@@ -61,18 +61,20 @@ bool small(const WalkWork &w) {
   return saves < 40 * (int64_t)w.steps + 50 * (int64_t)w.grids;
 }
 
-// Whether the estimates save at least 50 us of a walk over 16 million rows side
-// by side (ld = F): few deep trees over many features and ragged trees of one
-// or two splits do not (1 million rows, 10 trees of depth 9 over 128 features
-// 152 us against 209; 20 ragged stumps 168 against 390 at 1.5 million).
+// Whether the estimates ever choose the form: of 16 million rows, aligned or
+// not.  Few deep trees over many features and ragged trees of one or two
+// splits do not (1 million rows, 10 trees of depth 9 over 128 features 152 us
+// against 209; 20 ragged stumps 168 against 390 at 1.5 million).
 bool ever_pays(const Forest &f, const RankForm &r, int cu_count) {
-  const int64_t n = (int64_t)1 << 24;
+  const double n = 1 << 24;
   WalkPlan p;
   const char *why = nullptr;
-  if (!plan_walk(f, n, cu_count, &p, &why, false, false)) return false;
-  const RowKind kind = row_kind(f.num_features % 4 == 0, f.num_features);
-  return rank_walk_us(r.work, r.shape, kind, (double)n, cu_count) + 50.0 <
-         float_walk_us(r.work, float_shape(p), kind, (double)n, cu_count);
+  if (!plan_walk(f, (int64_t)n, cu_count, &p, &why, false, false)) return false;
+  for (bool aligned : {true, false}) {
+    const RowKind kind = row_kind(aligned, f.num_features);
+    if (rank_walk_wins(r.work, float_shape(p), r.shape, kind, n, cu_count)) return true;
+  }
+  return false;
 }
 
 }  // namespace
@@ -145,7 +147,7 @@ void rank_free(Forest *f) {
   f->rank = RankForm{};
 }
 
-// A walk ranks where the estimates say that it is the faster one, from three
+// A walk ranks where the estimates choose it, from three
 // quarters of a round of every CU on (196,608 rows with 16 waves a CU): below,
 // a walk takes as long as its longest lane, and the float walk's two lanes per
 // candidate and shorter start win (validity, 300 trees of depth 6 over 128
@@ -159,10 +161,10 @@ void rank_free(Forest *f) {
 // How many rows a mask accepts is known on the device only, and a walk over
 // few is the float walk's (300 trees of depth 6 over 128 features, 1 million
 // rows: 30,000 accepted 40 us against 87, 300,000 213 and 212, 600,000 368 and
-// 326).  Such a walk is priced at 15 % of its rows.  Of 7,400 timed ones, the
-// walk taken is more than 5 % slower than the float walk for 7 % of those with
-// 5 to 15 % accepted (priced at every row: 17 %), 1.6 % up to 35 % (3.3 %) and
-// 0.3 % above; the gain given away is 2 % on average.
+// 326).  Such a walk is priced at a fifth of its rows.  Of 7,500 timed ones, the
+// walk taken is more than 5 % slower than the float walk for 12 % of those with
+// 5 to 15 % accepted (priced at every row: 18 %), 3 % up to 35 % (4 %) and 1 %
+// above; a seventh instead gives away more above (5 instead of 3 % of the time).
 bool rank_takes(const Forest &f, const float *X, int64_t n, int64_t ld, const WalkPlan &plan,
                 bool perf, bool masked) {
   const RankForm &r = f.rank;
@@ -176,8 +178,7 @@ bool rank_takes(const Forest &f, const float *X, int64_t n, int64_t ld, const Wa
   const bool aligned = (reinterpret_cast<uintptr_t>(X) & 15u) == 0 && (ld & 3) == 0;
   const RowKind kind = row_kind(aligned, f.num_features);
   const double rows = masked ? masked_rows((double)n) : (double)n;
-  return rank_walk_us(r.work, r.shape, kind, rows, plan.cus) <
-         float_walk_us(r.work, float_shape(plan), kind, rows, plan.cus);
+  return rank_walk_wins(r.work, float_shape(plan), r.shape, kind, rows, plan.cus);
 }
 
 // The arguments of a launch over n rows.

@@ -93,7 +93,7 @@ RowKind row_kind(bool aligned, int32_t features) {
 // trees, 4 to 256 features in aligned and unaligned rows, 100,000 to 4 million
 // rows, 256 CUs.  Median error 6 to 10 %.  Of the 7,300 large enough to rank
 // (rank_takes), the walk taken with them is more than 5 % slower than the float
-// walk for 1 %, and for 8 % without them.
+// walk for 3 %, and for 8 % without them.
 double float_walk_us(const WalkWork &w, const FloatShape &s, RowKind kind, double rows, int cus) {
   struct Fit {
     double call, row[3], chunk, round, visit, chain;
@@ -111,8 +111,12 @@ double float_walk_us(const WalkWork &w, const FloatShape &s, RowKind kind, doubl
   const int chunks = (w.records + s.chunk - 1) / s.chunk;
   const double visits = w.ragged ? w.path : (double)w.records * w.depth;
   const double chain = visits / s.split / (w.ragged ? 1 : s.group);
+  // (copies: about 3,500 bytes per wave and microsecond)
+  const double chunk =
+      s.copied ? (double)s.chunk * record_bytes(w.ragged ? 0 : w.depth) / (3500.0 * s.waves)
+               : c.chunk;
   return c.call + rounds * (w.features * lanes * c.row[kind] +
-                            (chunks > 1 ? chunks * per_cu * c.chunk : 0.0) + c.round +
+                            (chunks > 1 ? chunks * per_cu * chunk : 0.0) + c.round +
                             visits * lanes * c.visit + chain * c.chain);
 }
 

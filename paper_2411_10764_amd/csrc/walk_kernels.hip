@@ -1738,6 +1738,7 @@ bool try_plan(const Forest &f, int64_t n_work, int cu_count, int S, int W, int m
   if (grid < 1) grid = 1;
   q.grid = (int)grid;
   q.cus = cu_count;
+  q.copied = mode == 2 ? 1 : 0;
   *p = q;
   return true;
 }
