@@ -74,6 +74,23 @@ ml2_status ml2_tune_walk_plan(int32_t split, int32_t group, int32_t waves, int32
  * Errors: INVALID_ARG outside 0..2. */
 ml2_status ml2_tune_layout(int32_t layout);
 
+/* The walk that a call over n rows at X (row stride ld) takes: with perf = 0
+ * ml2_score_validity, with perf = 1 ml2_score_perf, masked = 1 where it is
+ * given a mask.  X is not read (only its alignment counts). */
+typedef struct {
+  int32_t loaded; /* 1: the ensemble has a form of threshold codes */
+  int32_t codes;  /* 1: the call walks over codes, 0: over floats */
+  int32_t mode;   /* codes of 0 a byte, 1 a half-word, 2 packed fields */
+  int32_t depth;  /* of the perfect trees; 0: ragged trees */
+  int32_t waves;  /* largest workgroup */
+  int32_t per_cu; /* workgroups that share a compute unit */
+  int32_t group;  /* trees walked together by a lane */
+} ml2_walk_info;
+/* Errors: INVALID_ARG for a NULL pointer (X may be NULL), n < 1 or ld below
+ * the features; UNSUPPORTED where the call itself is. */
+ml2_status ml2_probe_walk(const ml2_ensemble *e, const float *X, int64_t n, int64_t ld,
+                          int32_t perf, int32_t masked, ml2_walk_info *info);
+
 #ifdef __cplusplus
 }
 #endif

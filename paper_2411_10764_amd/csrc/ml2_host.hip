@@ -988,6 +988,30 @@ ml2_status ml2_tune_layout(int32_t layout) {
   return ML2_OK;
 }
 
+ml2_status ml2_probe_walk(const ml2_ensemble *e, const float *X, int64_t n, int64_t ld,
+                          int32_t perf, int32_t masked, ml2_walk_info *info) {
+  if (!e || !info) return fail(ML2_ERR_INVALID_ARG, "ml2_probe_walk: NULL pointer");
+  if (n < 1 || n > (int64_t)INT32_MAX || ld < e->f.num_features)
+    return fail(ML2_ERR_INVALID_ARG, "ml2_probe_walk: n = %lld or ld = %lld out of range",
+                (long long)n, (long long)ld);
+  ml2::WalkPlan p;
+  const char *why = nullptr;
+  if (!ml2::plan_walk(e->f, n, cu_count(e->f.device), &p, &why, perf && masked))
+    return fail(ML2_ERR_UNSUPPORTED, "ml2_probe_walk: %s", why);
+  const ml2::RankForm &r = e->f.rank;
+  *info = ml2_walk_info{};
+  info->loaded = r.ok;
+  if (r.ok) {
+    info->codes = ml2::rank_takes(e->f, X, n, ld, p, perf != 0, perf && masked) ? 1 : 0;
+    info->mode = r.mode;
+    info->depth = e->f.ragged ? 0 : r.depth;
+    info->waves = r.shape.waves;
+    info->per_cu = r.shape.per_cu;
+    info->group = r.shape.group;
+  }
+  return ML2_OK;
+}
+
 // ---- microbenchmarks (ml2_probe.h) -------------------------------------------
 
 ml2_status ml2_probe_visit(int32_t depth, int32_t trees_per_lane, int32_t lanes_per_candidate,

@@ -40,7 +40,7 @@ EXPORTED = (
 )
 # include/ml2_probe.h: microbenchmarks behind the roofline figures
 EXPORTED_PROBE = ("ml2_probe_visit", "ml2_probe_lds", "ml2_probe_valu", "ml2_tune_walk_plan",
-                  "ml2_tune_layout")
+                  "ml2_tune_layout", "ml2_probe_walk")
 
 
 class Ml2Error(RuntimeError):
@@ -62,6 +62,11 @@ class ml2_ensemble_desc(ctypes.Structure):
         ("leaf_value", ctypes.c_void_p),
         ("default_left", ctypes.c_void_p),
     ]
+
+
+class ml2_walk_info(ctypes.Structure):
+    _fields_ = [(f, ctypes.c_int32) for f in
+                ("loaded", "codes", "mode", "depth", "waves", "per_cu", "group")]
 
 
 _lib = None
@@ -138,6 +143,8 @@ def lib():
         L.ml2_tune_walk_plan.argtypes = [I32, I32, I32, I32, I32]
         L.ml2_tune_layout.restype = I32
         L.ml2_tune_layout.argtypes = [I32]
+        L.ml2_probe_walk.restype = I32
+        L.ml2_probe_walk.argtypes = [P, P, I64, I64, I32, I32, ctypes.POINTER(ml2_walk_info)]
         _lib = L
     return _lib
 
@@ -463,3 +470,12 @@ def ml2_tune_layout(layout: int = 0) -> None:
     """Force the layout of later loads: 0 the loader's choice, 1 perfect,
     2 ragged (where the ensemble allows it)."""
     _check(lib().ml2_tune_layout(layout))
+
+
+def ml2_probe_walk(e: Ensemble, X, n: int, ld: int, perf: bool, masked: bool) -> ml2_walk_info:
+    """The walk that ml2_score_validity (perf: ml2_score_perf, masked: with a
+    mask) takes over n rows at X (a tensor or an address) with row stride ld."""
+    info = ml2_walk_info()
+    _check(lib().ml2_probe_walk(e.handle, _ptr(X), n, ld, int(perf), int(masked),
+                                ctypes.byref(info)))
+    return info

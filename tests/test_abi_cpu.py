@@ -62,6 +62,12 @@ def test_probe_argument_errors(call):
     assert ms.value == -1.0 and w.value == -1.0
 
 
+def test_probe_walk_argument_errors():
+    L, info = ml2.lib(), ml2.ml2_walk_info()
+    assert L.ml2_probe_walk(None, None, 1, 4, 0, 0, ctypes.byref(info)) == ml2.ML2_ERR_INVALID_ARG
+    assert b"NULL" in L.ml2_last_error()
+
+
 @pytest.mark.parametrize("args", [(-1, 0, 0, 0, 0), (3, 0, 0, 0, 0), (0, 17, 0, 0, 0),
                                   (0, 0, 9, 0, 0), (0, 0, 0, 3, 0), (0, 0, 0, 0, -4)])
 def test_tune_walk_plan_argument_errors(args):
