@@ -1646,7 +1646,6 @@ hipError_t launch_leaves_depth(const WalkArgs &a, int G, size_t lds, int row_til
   return hipErrorInvalidValue;
 }
 
-// (depths 10 to 12: leaves_gather_kernel)
 hipError_t launch_leaves(int depth, const WalkArgs &a, int G, size_t lds, int row_tiles,
                          hipStream_t s) {
   switch (depth) {
@@ -1660,6 +1659,9 @@ hipError_t launch_leaves(int depth, const WalkArgs &a, int G, size_t lds, int ro
     case 7: return launch_leaves_depth<7>(a, G, lds, row_tiles, s);
     case 8: return launch_leaves_depth<8>(a, G, lds, row_tiles, s);
     case 9: return launch_leaves_depth<9>(a, G, lds, row_tiles, s);
+    case 10: return launch_leaves_depth<10>(a, G, lds, row_tiles, s);
+    case 11: return launch_leaves_depth<11>(a, G, lds, row_tiles, s);
+    case 12: return launch_leaves_depth<12>(a, G, lds, row_tiles, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1977,10 +1979,21 @@ size_t rows_workspace_bytes(const Forest &f, int32_t m) {
 }
 
 // Perfect trees from this depth on are walked one per workgroup with their
-// rows' features gathered (leaves_gather_kernel).  The second level of 300
-// trees over 1,024 rows of an 8M x 128 pool, tiles against gathers: depth 12
-// 124 and 75 us, depth 10 74 and 64; 200 of depth 9 39 and 39.
+// rows' features gathered (leaves_gather_kernel): a short list always, a longer
+// one where four waves' tiles and two trees do not fit the LDS.  The second
+// level of 300 trees, tiles against gathers: 1,024 rows, depth 12 over 128
+// features 124 and 75 us, depth 10 74 and 64, over 16 features 22 and 34; 16,384
+// rows, depth 10 over 16 features 145 and 290 us, over 256 gathers take half as
+// long; 64 rows, gathers 10 to 30 % faster at any width.  200 of depth 9, 1,024
+// rows: 39 and 39.
 constexpr int kGatherDepth = 10;
+constexpr int kGatherList = 256;  // entries
+
+static bool gathers(const Forest &f, int32_t m) {
+  if (f.ragged || f.depth < kGatherDepth) return false;
+  const size_t tile = (size_t)f.num_features * Geo<1>::kRowBytes;
+  return m <= kGatherList || 4 * tile + 2 * (size_t)f.rec_bytes > kLdsBudget;
+}
 
 static hipError_t launch_fold(const WalkArgs &a, hipStream_t s) {
   hipLaunchKernelGGL(fold_kernel, dim3((unsigned)((a.n + kLanes - 1) / kLanes)),
@@ -1997,7 +2010,7 @@ hipError_t launch_rows(const Forest &f, const float *X, int64_t n, int64_t ld, c
   if (m <= 0) return hipSuccess;
   const size_t rb = f.rec_bytes;
   const int D = f.ragged ? 0 : f.depth;
-  if (D >= kGatherDepth) {
+  if (gathers(f, m)) {
     WalkArgs a{};
     a.X = X;
     a.n = m;

@@ -77,6 +77,32 @@ def test_rerank_places(trees, depth, m, shared):
     a.free()
 
 
+# deep trees: lists up to 256 entries and wide rows gather their features,
+# longer lists of narrow rows walk in tiles
+@pytest.mark.parametrize("trees,depth", [(9, 10), (5, 11), (3, 12)])
+@pytest.mark.parametrize("F", [20, 64, 130])
+@pytest.mark.parametrize("m", [1, 65, 256, 257, 1025])
+def test_rerank_deep(trees, depth, F, m):
+    n, keep = 3000, max(1, m // 2)
+    A = gen.perfect_ensemble(32, 3, trees, depth, F, F // 2, 0.1)
+    X = gen.features(32, n, F, F // 2)
+    rows = np.random.default_rng(m + F).integers(-3, n + 3, m).astype(np.int32)
+    want = oracle.rerank(A, X, rows, keep)
+    a = ml2.ml2_load_ensemble(A)
+    Xd, rd = torch.from_numpy(X).to(DEV), torch.from_numpy(rows).to(DEV)
+    rs, top = torch.empty(m, device=DEV), torch.empty(keep, device=DEV)
+    idx = torch.empty(keep, dtype=torch.int32, device=DEV)
+    num = torch.empty(1, dtype=torch.int32, device=DEV)
+    ws = torch.empty(ml2.ml2_rerank_workspace_bytes(a, m), dtype=torch.uint8, device=DEV)
+    ml2.ml2_rerank(a, Xd, rd, keep, rs, idx, top, num, ws)
+    torch.cuda.synchronize()
+    assert np.array_equal(rs.cpu().numpy().view(np.uint32), want[0].view(np.uint32))
+    assert np.array_equal(idx.cpu().numpy(), want[1])
+    assert np.array_equal(top.cpu().numpy().view(np.uint32), want[2].view(np.uint32))
+    assert int(num.item()) == want[3]
+    a.free()
+
+
 # held and chunk lists of every fill, chunks that overlap in part and wholly
 @pytest.mark.parametrize("k", [1, 5, 64, 1000, 4096])
 def test_stream_merge(k):
