@@ -94,6 +94,7 @@ void pack_ragged(const std::vector<TreeView> &views, const std::vector<int> &dep
   };
   size_t t = 0;
   int32_t tree_index = 0;
+  uint32_t node0 = 0;  // nodes of the trees before
   while (t < views.size()) {
     // choose the trees of this slot: header + roots + 8 bytes per node,
     // with room left for padding the tree count to a multiple of GRP
@@ -129,6 +130,7 @@ void pack_ragged(const std::vector<TreeView> &views, const std::vector<int> &dep
       put_root(i, head / 8u + next);
       if (i >= real) {  // padding: one leaf of value -0.0
         put(next, leaf_word0(head / 8u + next + 1), float_bits(-0.0f));
+        out->origin.push_back(0);
         ++next;
         continue;
       }
@@ -150,6 +152,7 @@ void pack_ragged(const std::vector<TreeView> &views, const std::vector<int> &dep
       for (size_t k = 0; k < order.size(); ++k) {
         const int32_t o = order[k];
         const uint32_t j = next + (uint32_t)k;
+        out->origin.push_back(node0 + (uint32_t)o);
         if (tv.left[o] == -1) {
           put(j, leaf_word0(head / 8u + next + (uint32_t)order.size()), float_bits(tv.val[o]));
         } else {
@@ -164,12 +167,14 @@ void pack_ragged(const std::vector<TreeView> &views, const std::vector<int> &dep
         }
       }
       next += (uint32_t)order.size();
+      node0 += (uint32_t)tv.size;
     }
     // the sentinel: a leaf of value -0.0 that the two entries after the last
     // root point to (a walk past its last tree moves onto it; adding -0.0
     // changes no float)
     const uint32_t sentinel = head / 8u + next;
     put(next, leaf_word0(sentinel), float_bits(-0.0f));
+    out->origin.push_back(0);
     put_root(ntr, sentinel);
     put_root(ntr + 1, sentinel);
     ++next;

@@ -38,6 +38,9 @@ struct RaggedPack {
   int32_t slots = 0;
   int32_t trees = 0;  // with the padding trees
   int32_t depth = 0;  // deepest path over all trees
+  // per node of the slots in order: its number among all trees' nodes (padding
+  // and sentinels: 0)
+  std::vector<uint32_t> origin;
 };
 void pack_ragged(const std::vector<TreeView> &views, const std::vector<int> &depths,
                  RaggedPack *out);

@@ -8,6 +8,7 @@
 
 #include <algorithm>
 #include <memory>
+#include <new>
 
 namespace ml2 {
 namespace {
@@ -46,17 +47,20 @@ constexpr size_t kMostThresholds = 65535 - 8192;
 // e (passes even) or tmp.
 template <int B>
 void radix_passes(Entry *e, Entry *tmp, size_t n, int passes) {
+  constexpr int kMost = 4;
+  constexpr uint32_t mask = (1u << B) - 1;
+  uint32_t count[kMost][1 << B] = {{0}};
+  for (size_t i = 0; i < n; ++i)
+    for (int pass = 0; pass < passes; ++pass) ++count[pass][(e[i].key >> (pass * B)) & mask];
   for (int pass = 0; pass < passes; ++pass) {
-    uint32_t count[1 << B] = {0};
-    const int sh = pass * B;
-    for (size_t i = 0; i < n; ++i) ++count[(e[i].key >> sh) & ((1u << B) - 1)];
     uint32_t at = 0;
-    for (uint32_t &c : count) {
+    for (uint32_t &c : count[pass]) {
       const uint32_t k = c;
       c = at;
       at += k;
     }
-    for (size_t i = 0; i < n; ++i) tmp[count[(e[i].key >> sh) & ((1u << B) - 1)]++] = e[i];
+    for (size_t i = 0; i < n; ++i)
+      tmp[count[pass][(e[i].key >> (pass * B)) & mask]++] = e[i];
     std::swap(e, tmp);
   }
 }
@@ -75,29 +79,62 @@ void sort_entries(Entry *e, Entry *tmp, size_t n) {
   }
 }
 
+// The exponent of the lowest set bit of v (not 0): v is a multiple of 2^that.
+int low_bit(float v) {
+  const uint32_t b = bits_of(v), e = (b >> 23) & 0xFFu;
+  const uint32_t m = (b & 0x7FFFFFu) | (e ? 0x800000u : 0u);
+  return (int)(e ? e : 1u) - 150 + __builtin_ctz(m);
+}
+
 // The grid of a sorted list of distinct thresholds: multiples of a power of
 // two h <= 1 whose range holds at most `most` points.  h is not above 1, so
 // x / h never rounds towards zero (no underflow) and floor(x / h) < t / h
-// exactly when x < t; overflow to infinity keeps the order.
+// exactly when x < t; overflow to infinity keeps the order.  Most lists that
+// have none are known by their first few thresholds.
 bool find_grid(const std::vector<float> &t, int most, RankGrid *g) {
+  if (!std::isfinite(t.front()) || !std::isfinite(t.back())) return false;
+  const double range = (double)t.back() - (double)t.front();
   int e = 0;  // h = 2^e
   for (float v : t) {
-    if (!std::isfinite(v)) return false;
-    if (v == 0.0f) continue;
-    int x;
-    const double m = frexp((double)v, &x);  // v = m * 2^x, m a multiple of 2^-24
-    const int64_t q = (int64_t)ldexp(m, 24);
-    int low = x - 24;
-    for (int64_t w = q < 0 ? -q : q; (w & 1) == 0; w >>= 1) ++low;
-    if (low < e) e = low;
+    if (v == 0.0f || low_bit(v) >= e) continue;
+    e = low_bit(v);
+    if (e < -100 || ldexp(range, -e) + 1.0 > (double)most) return false;
   }
-  if (e < -100) return false;
   const double lo = ldexp((double)t.front(), -e), hi = ldexp((double)t.back(), -e);
   if (fabs(lo) > 4194304.0 || fabs(hi) > 4194304.0 || hi - lo + 1.0 > (double)most) return false;
   g->scale = (float)ldexp(1.0, -e);
   g->bias = (float)(1.0 - lo);
   g->top = (float)(hi - lo + 1.0);
   return true;
+}
+
+// Keys of n entries that have at most kFewKeys distinct ones: those, ascending,
+// and place[i] the one of entry i; 0 where there are more.  (The splits on a
+// knob of nine values have nine thresholds: 4 ns an entry, 25 by sorting.)
+constexpr int kFewKeys = 24;
+int few_keys(const Entry *e, size_t n, uint32_t (&keys)[kFewKeys], uint8_t *place) {
+  constexpr int kBuckets = 64;
+  uint32_t seen[kFewKeys];
+  int8_t bucket[kBuckets];  // an index into seen, -1: none
+  memset(bucket, -1, sizeof bucket);
+  int m = 0;
+  for (size_t i = 0; i < n; ++i) {
+    const uint32_t key = e[i].key;
+    uint32_t h = (key * 0x9E3779B1u) >> 26;
+    while (bucket[h] >= 0 && seen[bucket[h]] != key) h = (h + 1) % kBuckets;
+    if (bucket[h] < 0) {
+      if (m == kFewKeys) return 0;
+      bucket[h] = (int8_t)m;
+      seen[m++] = key;
+    }
+    place[i] = (uint8_t)bucket[h];
+  }
+  std::copy(seen, seen + m, keys);
+  std::sort(keys, keys + m);
+  uint8_t at[kFewKeys];
+  for (int j = 0; j < m; ++j) at[j] = (uint8_t)(std::lower_bound(keys, keys + m, seen[j]) - keys);
+  for (size_t i = 0; i < n; ++i) place[i] = at[place[i]];
+  return m;
 }
 
 // The node of a split: its feature's half-word and the comparand of code t.
@@ -177,13 +214,13 @@ int steps_of(size_t n) {
 // n sorted thresholds as a search tree of s levels, breadth-first from entry
 // 1, padded with +inf.
 void put_search_tree(const float *t, size_t n, int s, char *dst) {
-  const size_t size = (size_t)1 << s;
   memset(dst, 0, 4);
-  for (size_t u = 1; u < size; ++u) {
-    const int l = steps_of(u) - 1;  // its level
-    const size_t in_order = (((u - ((size_t)1 << l)) * 2 + 1) << (s - 1 - l)) - 1;
-    const float v = in_order < n ? t[in_order] : INFINITY;
-    memcpy(dst + 4 * u, &v, 4);
+  for (int l = 0; l < s; ++l) {
+    for (size_t i = 0; i < (size_t)1 << l; ++i) {  // entries of level l, left to right
+      const size_t in_order = ((2 * i + 1) << (s - 1 - l)) - 1;
+      const float v = in_order < n ? t[in_order] : INFINITY;
+      memcpy(dst + 4 * (((size_t)1 << l) + i), &v, 4);
+    }
   }
 }
 
@@ -304,7 +341,9 @@ void lay_out_tables(const RankCodes &codes, int num_features, uint32_t slot_byte
 // Room for the slots, and the tables in them.
 void put_tables(const std::vector<Table> &tables, uint32_t slot_bytes, RankPack *out) {
   out->bytes = (size_t)out->slots * slot_bytes;
-  out->data.reset(new char[out->bytes]);  // bytes between tables and trees stay unset, unread
+  // (bytes between tables and trees stay zero)
+  out->data.reset(static_cast<char *>(calloc(out->bytes, 1)));
+  if (!out->data) throw std::bad_alloc();
   parallel_for((int64_t)tables.size(), (int64_t)tables.size() * 512, [&](int64_t i) {
     const Table &t = tables[(size_t)i];
     put_search_tree(t.t, t.n, t.steps,
@@ -362,10 +401,17 @@ bool rank_codes(const std::vector<TreeView> &views, int num_features, RankCodes 
     const size_t f = (size_t)fi, n = first[f + 1] - first[f];
     if (n == 0) return;
     Entry *e = all.get() + first[f];
-    sort_entries(e, tmp.get() + first[f], n);
     std::vector<float> &t = out->table[f];
-    for (size_t i = 0; i < n; ++i)
-      if (i == 0 || e[i].key != e[i - 1].key) t.push_back(value_of(e[i].key));
+    uint32_t keys[kFewKeys];
+    uint8_t *place = reinterpret_cast<uint8_t *>(tmp.get() + first[f]);
+    const int few = few_keys(e, n, keys, place);
+    if (few) {
+      for (int j = 0; j < few; ++j) t.push_back(value_of(keys[j]));
+    } else {
+      sort_entries(e, tmp.get() + first[f], n);
+      for (size_t i = 0; i < n; ++i)
+        if (i == 0 || e[i].key != e[i - 1].key) t.push_back(value_of(e[i].key));
+    }
     const size_t n_t = t.size();
     if (n_t > kMostThresholds) {
       too_many[f] = 1;
@@ -375,11 +421,17 @@ bool rank_codes(const std::vector<TreeView> &views, int num_features, RankCodes 
     // that a byte holds (a table costs a search)
     RankGrid g{};
     const bool grid = find_grid(t, n_t <= 255 ? 255 : n_t <= 4095 ? 4095 : 65535, &g);
-    uint32_t c = 0;
-    for (size_t i = 0, j = 0; i < n; ++i) {
-      if (i == 0 || e[i].key != e[i - 1].key)
-        c = grid ? (uint32_t)((double)t[j++] * g.scale + g.bias) : (uint32_t)++j;
-      out->code[e[i].node] = (uint16_t)c;
+    auto code_of = [&](size_t j) {  // of threshold j
+      return (uint16_t)(grid ? (uint32_t)((double)t[j] * g.scale + g.bias) : (uint32_t)j + 1);
+    };
+    if (few) {
+      for (size_t i = 0; i < n; ++i) out->code[e[i].node] = code_of(place[i]);
+    } else {
+      uint16_t c = 0;
+      for (size_t i = 0, j = 0; i < n; ++i) {
+        if (i == 0 || e[i].key != e[i - 1].key) c = code_of(j++);
+        out->code[e[i].node] = c;
+      }
     }
     codes[f] = grid ? (size_t)g.top : n_t;
     if (grid) {
@@ -473,6 +525,7 @@ bool rank_pack_ragged(const RaggedPack &ragged, const RankCodes &codes, int num_
   char *dst0 = out->data.get() + (size_t)slot0 * SB;
   memcpy(dst0, ragged.bytes.data(), (size_t)ragged.slots * SB);
   const uint32_t unit = codes.mode == kRankByte ? 256u : 8u;
+  const uint32_t *origin = ragged.origin.data();
   for (int s = 0; s < ragged.slots; ++s) {
     char *slot = dst0 + (size_t)s * SB;
     uint32_t head[4];  // trees, deepest path, the sentinel's node, first tree
@@ -480,20 +533,14 @@ bool rank_pack_ragged(const RaggedPack &ragged, const RankCodes &codes, int num_
     out->chunks.push_back({slot0 + s, 0, (int32_t)head[0], 0});
     uint32_t node;
     memcpy(&node, slot + 16, 4);  // the first root: the first node
-    for (; node <= head[2]; ++node) {
+    for (; node <= head[2]; ++node, ++origin) {
       uint32_t w[2];
       memcpy(w, slot + 8 * (size_t)node, 8);
       if ((w[0] >> 16) == 0x7FFFu) {
         w[0] = (w[0] << 16) | 0xFFFFu;
       } else {
         const uint32_t left = node + ((w[0] >> 16) & 0x7FFFu), f = (w[0] >> 8) & 0xFFu;
-        const float t = float_of(w[1]);
-        const RankGrid &g = codes.grid[f];
-        const std::vector<float> &tab = codes.table[f];
-        const uint32_t code =  // x < t exactly when code(x) < code
-            g.top != 0.0f ? (uint32_t)((double)t * g.scale + g.bias)
-                          : (uint32_t)(std::lower_bound(tab.begin(), tab.end(), t) -
-                                       tab.begin()) + 1;
+        const uint32_t code = codes.code[*origin];  // x < t exactly when code(x) < code
         const bool default_left = (w[0] >> 31) != 0;
         w[0] = (8u * left << 16) | (unit * (default_left ? code : code - 1));
         w[1] = ((default_left ? unit : 0u) << 16) | codes.field[f].off;

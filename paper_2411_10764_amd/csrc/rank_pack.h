@@ -40,6 +40,7 @@
 #pragma once
 
 #include <stdint.h>
+#include <stdlib.h>
 
 #include <memory>
 #include <vector>
@@ -87,12 +88,15 @@ struct RankChunk {    // trees of one slot
   int32_t slot, offset, trees, pad;
 };
 
+struct FreeBytes {
+  void operator()(char *p) const { free(p); }
+};
 struct RankPack {
   RankMode mode = kRankByte;
   int lines = 0, slots = 0, group = 0;
   uint32_t rows = 0;                   // dword rows of the tile
   size_t bytes = 0;                    // slots * slot_bytes
-  std::unique_ptr<char[]> data;
+  std::unique_ptr<char[], FreeBytes> data;
   std::vector<RankGrid> grid;          // lines * kRankLine
   std::vector<int32_t> line_group;     // lines + 1: first group of each line
   std::vector<int32_t> group_slot;
