@@ -5,16 +5,89 @@
 
 #include <algorithm>
 #include <atomic>
+#include <condition_variable>
 #include <exception>
-#include <system_error>
+#include <functional>
+#include <mutex>
 #include <thread>
+#include <utility>
 #include <vector>
 
 namespace ml2 {
 
-// fn(i) for i in [0, n) on up to eight threads; work: the nodes handled in
-// all, since fewer than 32,768 are done before a thread has started.  The
-// first exception of fn is rethrown once every thread has ended.
+// The threads that the loops of one thread's scope share: started by the first
+// loop that wants them, waiting between loops, joined at the scope's end
+// (starting and joining them took a loop 50 us a thread).
+class Team {
+ public:
+  Team() : outer_(std::exchange(current(), this)) {}
+  ~Team() {
+    current() = outer_;
+    {
+      std::lock_guard<std::mutex> lock(mu_);
+      stop_ = true;
+    }
+    wake_.notify_all();
+    for (std::thread &t : threads_) t.join();
+  }
+  Team(const Team &) = delete;
+  Team &operator=(const Team &) = delete;
+
+  // The innermost team of this thread, or nullptr.
+  static Team *&current() {
+    static thread_local Team *team = nullptr;
+    return team;
+  }
+
+  // job() here and on up to `helpers` threads; returns when every call has.  A
+  // thread that comes too late for the job does not hold it up.
+  void run(int helpers, const std::function<void()> &job) {
+    try {
+      while ((int)threads_.size() < helpers) threads_.emplace_back([this] { loop(); });
+    } catch (...) {  // no more threads, or no memory for them: fewer do the work
+    }
+    {
+      std::lock_guard<std::mutex> lock(mu_);
+      job_ = &job;
+      wanted_ = helpers;
+    }
+    wake_.notify_all();
+    job();
+    std::unique_lock<std::mutex> lock(mu_);
+    wanted_ = 0;
+    idle_.wait(lock, [this] { return active_ == 0; });
+    job_ = nullptr;
+  }
+
+ private:
+  void loop() {
+    std::unique_lock<std::mutex> lock(mu_);
+    for (;;) {
+      wake_.wait(lock, [this] { return stop_ || wanted_ > 0; });
+      if (stop_) return;
+      --wanted_;
+      ++active_;
+      const std::function<void()> *job = job_;
+      lock.unlock();
+      (*job)();
+      lock.lock();
+      if (--active_ == 0) idle_.notify_one();
+    }
+  }
+
+  Team *outer_;
+  std::mutex mu_;
+  std::condition_variable wake_, idle_;
+  std::vector<std::thread> threads_;
+  const std::function<void()> *job_ = nullptr;
+  int wanted_ = 0, active_ = 0;  // threads the job still takes; those in it
+  bool stop_ = false;
+};
+
+// fn(i) for i in [0, n) on up to eight threads (of the current team, if there
+// is one); work: the nodes handled in all, since fewer than 32,768 are done
+// before a thread has started.  The first exception of fn is rethrown once
+// every thread has ended.
 template <typename Fn>
 void parallel_for(int64_t n, int64_t work, Fn fn) {
   const int64_t most = std::min<int64_t>(
@@ -30,14 +103,15 @@ void parallel_for(int64_t n, int64_t work, Fn fn) {
       if (!failed.exchange(true)) error = std::current_exception();
     }
   };
-  std::vector<std::thread> threads;
-  try {
-    threads.reserve((size_t)std::max<int64_t>(most, 1));
-    for (int64_t t = 1; t < most; ++t) threads.emplace_back(run);
-  } catch (...) {  // no more threads, or no memory for them: fewer do the work
+  if (most < 2) {
+    run();
+  } else if (Team *team = std::exchange(Team::current(), nullptr)) {  // (fn's own loops stay here)
+    team->run((int)most - 1, std::ref(run));
+    Team::current() = team;
+  } else {
+    Team alone;
+    alone.run((int)most - 1, std::ref(run));
   }
-  run();
-  for (std::thread &t : threads) t.join();
   if (error) std::rethrow_exception(error);
 }
 

@@ -275,6 +275,7 @@ ml2_status ml2_load_ensemble(const ml2_ensemble_desc *desc, ml2_ensemble **out) 
   if (d.tree_node_offset[0] != 0)
     return fail(ML2_ERR_INVALID_ARG, "tree_node_offset[0] = %lld, expected 0",
                 (long long)d.tree_node_offset[0]);
+  ml2::Team team;  // of the loops below
   int depth = 1;
   double max_leaf = 0.0, path = 0.0;
   int64_t total_nodes = 0, max_nodes = 0;

@@ -19,12 +19,12 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(os.path.dirname(HERE), "paper_2411_10764_amd", "csrc")
 
 
-def _run_driver(tmp_path, name, sources):
+def _run_driver(tmp_path, name, sources, sanitize="address,undefined"):
     gxx = shutil.which("g++")
     if gxx is None:
         pytest.skip("g++ not available")
     exe = str(tmp_path / name)
-    r = subprocess.run([gxx, "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined",
+    r = subprocess.run([gxx, "-std=c++17", "-O1", "-g", "-fsanitize=" + sanitize,
                         "-fno-sanitize-recover=all", "-ffp-contract=off", "-Wall", "-Werror",
                         "-I", CSRC, os.path.join(HERE, name + ".cpp"),
                         *(os.path.join(CSRC, s) for s in sources), "-pthread", "-o", exe],
@@ -48,3 +48,8 @@ def test_every_tile_and_depth_has_a_launch_shape(tmp_path):
     whole slots within the LDS; the estimates choose the faster of two measured
     walks (tests/rank_plan_driver.cpp)."""
     assert _run_driver(tmp_path, "rank_plan_driver", ["rank_plan.cpp"]).strip() == "ok"
+
+
+def test_loading_loops(tmp_path):
+    """host_parallel.h under the thread sanitizer (tests/host_parallel_driver.cpp)."""
+    assert _run_driver(tmp_path, "host_parallel_driver", [], "thread").strip() == "ok"
