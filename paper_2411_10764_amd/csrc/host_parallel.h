@@ -85,13 +85,16 @@ class Team {
 };
 
 // fn(i) for i in [0, n) on up to eight threads (of the current team, if there
-// is one); work: the nodes handled in all, since fewer than 32,768 are done
-// before a thread has started.  The first exception of fn is rethrown once
-// every thread has ended.
+// is one); work: the nodes handled in all, of which a thread takes 16,384 at
+// least.  Fewer than 65,536 are done here: the threads' first touch of them
+// costs more than it saves (loading 300 trees of depth 6, 38,100 nodes: 0.8 ms
+// on two threads, 0.5 on one).  The first exception of fn is rethrown once every
+// thread has ended.
 template <typename Fn>
 void parallel_for(int64_t n, int64_t work, Fn fn) {
+  const int64_t threads = work < 65536 ? 1 : work / 16384;
   const int64_t most = std::min<int64_t>(
-      {n, 8, (int64_t)std::max(1u, std::thread::hardware_concurrency()), work / 16384});
+      {n, 8, (int64_t)std::max(1u, std::thread::hardware_concurrency()), threads});
   std::atomic<int64_t> next{0};
   std::exception_ptr error;
   std::atomic<bool> failed{false};
