@@ -34,9 +34,7 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0
 # Node-visit ceiling of the chip for the float walks, from its unit counts and
-# clock (256 CUs, 2.4 GHz); large pools are walked over threshold codes
-# (rank_walk.h), whose nodes take 4 bytes and codes 1 or 2, and are reported
-# against the same ceiling.  A float visit needs, per lane, two LDS reads (the 8-byte node and the
+# clock (256 CUs, 2.4 GHz).  A float visit needs, per lane, two LDS reads (the 8-byte node and the
 # 4-byte feature value) and, as counted on the walks (SQ_INSTS_VALU per
 # wave-visit: 5.01 in the perf walk, 5.27 in the validity walk), five VALU
 # instructions (node address, feature address, the comparison
@@ -51,12 +49,19 @@ HBM_PEAK_GBS = 8000.0
 # the float walk loop's measured rate at the shape a float walk of the pool
 # takes (the probe of --probe: the loop over a resident chunk, no row loads or
 # restaging).
+# Large pools are walked over threshold codes (rank_walk.h): two LDS reads a
+# visit of 4 bytes and 1 or 2, bound by the reads' rate and not their bytes.  A
+# CU takes a conflict-free 64-lane read in 2.75 clocks (measured), so
+# 256 CU x 64 x 2.4 GHz / (2 x 2.75) = 7.15 T visits/s; such walks are reported
+# against that, and have no float loop beside them.
 VALU_LANE_OPS_PER_S = 256 * 128 * 2.4e9
 VALU_PER_VISIT = 5
 VISIT_PEAK_VALU = VALU_LANE_OPS_PER_S / VALU_PER_VISIT
 LDS_BYTES_PER_S = 256 * 256 * 2.4e9
 VISIT_PEAK_LDS = LDS_BYTES_PER_S / 12
 VISIT_PEAK_PER_S = min(VISIT_PEAK_VALU, VISIT_PEAK_LDS)
+LDS_CLOCKS_PER_READ = 2.75
+CODE_VISIT_PEAK_PER_S = 256 * 64 * 2.4e9 / (2 * LDS_CLOCKS_PER_READ)
 MALL_BYTES = 256 << 20  # MI355X Infinity Cache: pools below it are flushed between steps
 # The float perf walk's launch shape (depth, trees per lane, lanes per candidate,
 # waves, features) where the walk-loop probe is built for it: the 16M pool,
@@ -645,25 +650,39 @@ def main() -> int:
                       fused, traffic if fused else None, copy_gbs)
         res["config"].update(launch)
         return _print(res)
-    shape = PERF_WALK_SHAPE.get(w.name)
+    # which walks the calls took: over codes or floats
+    def over_codes(ens, perf):
+        if fused:
+            return False
+        return bool(ml2.ml2_probe_walk(ens, X, w.n, X.stride(0), perf, perf).codes)
+
+    codes_v, codes_p = over_codes(v, False), over_codes(p, True)
+    peak_v = CODE_VISIT_PEAK_PER_S if codes_v else VISIT_PEAK_PER_S
+    peak_p = CODE_VISIT_PEAK_PER_S if codes_p else VISIT_PEAK_PER_S
+    shape = None if codes_p else PERF_WALK_SHAPE.get(w.name)
     loop = walk_loop_ceiling(shape) * 1e12 if shape else None
-    vshape = None if fused else VALIDITY_WALK_SHAPE.get(w.name)
+    vshape = None if fused or codes_v else VALIDITY_WALK_SHAPE.get(w.name)
     vloop = walk_loop_ceiling(vshape) * 1e12 if vshape else None
     v_visits_per_s = visits_v / (t_val / 1000.0)
     roofline = {
         "bound": "alu",
         "limiter": "lds",
         "kernel": ("fused_kernel (V then P on every row, one pass over the pool)" if fused
-                   else "performance walk (model P over accepted candidates)"),
-        "peak_derivation": "node visits on chip (LDS + VALU, no HBM or MFMA term): LDS 256 "
+                   else "performance walk (model P over accepted candidates, "
+                        + ("over codes)" if codes_p else "over floats)")),
+        "peak_derivation": ("node visits over codes: two 64-lane LDS reads a visit at the "
+                           f"measured {LDS_CLOCKS_PER_READ} clocks of a CU each, 256 CU x 64 x "
+                           f"2.4 GHz / {2 * LDS_CLOCKS_PER_READ} = "
+                           f"{CODE_VISIT_PEAK_PER_S / 1e12:.2f} T/s") if codes_p else
+                           "node visits on chip (LDS + VALU, no HBM or MFMA term): LDS 256 "
                            "B/clk/CU x 256 CU x 2.4 GHz / 12 B per visit = "
                            f"{VISIT_PEAK_LDS / 1e12:.1f} T/s; VALU 128 lanes/clk/CU x 256 CU x "
                            f"2.4 GHz / {VALU_PER_VISIT} instructions per visit (counted) = "
                            f"{VISIT_PEAK_VALU / 1e12:.1f} T/s; peak = the lower (LDS)",
         "achieved": perf_visits_per_s / 1e12,
-        "peak": VISIT_PEAK_PER_S / 1e12,
+        "peak": peak_p / 1e12,
         "unit": "Tvisit/s",
-        "frac": perf_visits_per_s / VISIT_PEAK_PER_S,
+        "frac": perf_visits_per_s / peak_p,
         "traffic": traffic,
         "traffic_unit": "bytes per launch (HBM read + write, copy-calibrated rocprofv3 counters)",
         "work_per_launch": (f"{visits_p} node visits ({w.n} rows x ({w.v_trees} + {w.p_trees}) "
@@ -680,7 +699,8 @@ def main() -> int:
                              if loop else None),
         "validity_kernel": (None if fused else
                             {"achieved": v_visits_per_s / 1e12, "launch_ms": t_val,
-                             "frac": v_visits_per_s / VISIT_PEAK_PER_S,
+                             "codes": codes_v, "peak": peak_v / 1e12,
+                             "frac": v_visits_per_s / peak_v,
                              "measured_ceiling": (
                                  {"achieved": vloop / 1e12, "frac": v_visits_per_s / vloop,
                                   "what": "float walk loop alone at a float validity walk's shape "
