@@ -73,7 +73,8 @@ VALIDITY_WALK_SHAPE = {"roofline": (6, 8, 2, 8, 128), "explorer": (6, 8, 1, 8, 6
                        "skewed": (6, 8, 1, 8, 64)}
 METRIC = "candidate configs scored+filtered/sec (validity+perf+top-k); % of HBM peak"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "walk_traffic_16m.json")
-KERNEL_SOURCE = os.path.join(ROOT, "paper_2411_10764_amd", "csrc", "walk_kernels.hip")
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_2411_10764_amd", "csrc", f)
+                  for f in ("walk_kernels.hip", "rank_walk.h", "rank_plan.h", "rank_plan.cpp")]
 
 
 def _log(msg: str) -> None:
@@ -81,8 +82,11 @@ def _log(msg: str) -> None:
 
 
 def _kernel_sha() -> str:
-    with open(KERNEL_SOURCE, "rb") as fh:
-        return hashlib.sha256(fh.read()).hexdigest()
+    sha = hashlib.sha256()
+    for f in KERNEL_SOURCES:
+        with open(f, "rb") as fh:
+            sha.update(fh.read())
+    return sha.hexdigest()
 
 
 def _traffic(kernel_sha: str, workload: str):

@@ -92,7 +92,9 @@ typedef struct ml2_ensemble ml2_ensemble; /* opaque; immutable after load */
  * (Table 3's depth-14 models trained on the paper's data are far smaller).
  * Loading also builds a second form, walked by large pools, in which every
  * threshold is replaced by its rank among its feature's thresholds (where it
- * pays, and memory allows; the results are the same).
+ * pays, and memory allows; the results are the same).  It is a second copy in
+ * device memory: 8 bytes for every 12 of perfect padded trees, as many as the
+ * chunks of the others, and 4 to 8 for each distinct threshold of a feature.
  */
 typedef struct {
   int32_t num_trees;

@@ -6,7 +6,7 @@
 // lane adds -0.0 on the slot's sentinel.  A step is a chain: the node's read,
 // the code's read, and the instructions that pick the next node between them.
 // Codes shorten both sides of it.  A byte per feature lets 24 waves share a CU
-// where float tiles of 64 features let eight, and the step takes eleven
+// where float tiles of 64 features let eight, and the step takes ten
 // vector instructions instead of nineteen: the direction is one saturated
 // subtraction and a minimum, 0 or 8, added to the child's offset, with the
 // missing value's way folded into the code by an addition modulo 2^16.

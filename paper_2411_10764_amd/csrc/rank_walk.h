@@ -16,15 +16,16 @@
 //
 // Why codes: a float tile of 128 features lets eight waves hold 32 candidates
 // each, a packed tile sixteen waves of 64, so the ensemble is staged for four
-// times the candidates, in nodes of four bytes instead of eight.  And a node visit takes its place in the two
-// units that bound it:
+// times the candidates, in nodes of four bytes instead of eight.  And a node
+// visit takes its place in the two units that bound it:
 //   LDS    4-byte node reads and column-owned code reads: about 2.9 clocks
 //          per 64-lane read (8-byte nodes at random: 10.7);
-//   VALU   address, shift, subtract, minimum and multiply-add in place of
-//          address, compare, add-with-carry and address: 15 instead of 19
-//          clocks of a SIMD per visit.  v_cmp, v_addc and v_lshl_add issue at half the
-//          rate of v_sub_u16, v_min_u16 and v_fmac_f32 (measured: 4.7 and
-//          2.7 clocks per 64-lane instruction).
+//   VALU   address, shift (packed codes), subtract, minimum and multiply-add
+//          (two from the sixth level on) in place of address, compare,
+//          add-with-carry and address: 15 to 18 instead of 19 clocks of a SIMD
+//          per visit.  v_cmp, v_addc and v_lshl_add issue at half the rate of
+//          v_sub_u16, v_min_u16 and v_fmac_f32 (measured: 4.7 and 2.7 clocks
+//          per 64-lane instruction).
 #pragma once
 
 #include <math.h>

@@ -44,7 +44,7 @@ constexpr int kBins = 1 << kDigitBits;
 constexpr int kMaxPasses = 6;    // 5 x 12 + 4 bits
 constexpr int kSelThreads = 512;
 constexpr int kSortThreads = 1024;
-constexpr int kInCap = 8192;     // keys of the threshold bin finished in one workgroup
+constexpr int kInCap = 8192;     // keys of the threshold bin that topk_finish places
 constexpr int kSmallN = 8192;    // pools selected in one launch of one workgroup
 constexpr int kTile = 1024;      // candidates a wave reads per step (16 per lane)
 constexpr size_t kStateBytes = 256;
