@@ -86,7 +86,11 @@ ml2_status fail(ml2_status st, const char *fmt, ...) {
   va_start(ap, fmt);
   vsnprintf(buf, sizeof buf, fmt, ap);
   va_end(ap);
-  g_last_error = buf;
+  try {
+    g_last_error = buf;
+  } catch (const std::bad_alloc &) {  // the status still tells
+    g_last_error.clear();
+  }
   return st;
 }
 
@@ -255,11 +259,11 @@ hipError_t ensure_dynamic_lds(const void *fn, size_t bytes) {
 
 }  // namespace ml2
 
-extern "C" {
+namespace {
 
-const char *ml2_last_error(void) { return g_last_error.c_str(); }
-
-ml2_status ml2_load_ensemble(const ml2_ensemble_desc *desc, ml2_ensemble **out) {
+// ml2_load_ensemble, but for host memory that is missing (std::bad_alloc;
+// nothing is on the device then).
+ml2_status load_ensemble(const ml2_ensemble_desc *desc, ml2_ensemble **out) {
   if (!out) return fail(ML2_ERR_INVALID_ARG, "ml2_load_ensemble: out is NULL");
   *out = nullptr;
   if (!desc) return fail(ML2_ERR_INVALID_ARG, "ml2_load_ensemble: desc is NULL");
@@ -297,14 +301,10 @@ ml2_status ml2_load_ensemble(const ml2_ensemble_desc *desc, ml2_ensemble **out) 
                  d.leaf_value + a,      d.default_left ? d.default_left + a : nullptr,
                  b - a};
   }
-  try {
-    ml2::parallel_for(ranged, ranged ? d.tree_node_offset[ranged] : 0, [&](int64_t t) {
-      bad[(size_t)t] = check_tree(d, (int32_t)t, views[(size_t)t], &depths[(size_t)t],
-                                  &leaf_of[(size_t)t], &path_of[(size_t)t]) != ML2_OK;
-    });
-  } catch (const std::bad_alloc &) {
-    return fail(ML2_ERR_OUT_OF_MEMORY, "host memory for checking the trees");
-  }
+  ml2::parallel_for(ranged, ranged ? d.tree_node_offset[ranged] : 0, [&](int64_t t) {
+    bad[(size_t)t] = check_tree(d, (int32_t)t, views[(size_t)t], &depths[(size_t)t],
+                                &leaf_of[(size_t)t], &path_of[(size_t)t]) != ML2_OK;
+  });
   for (int32_t t = 0; t < d.num_trees; ++t) {
     if (t == ranged)
       return fail(ML2_ERR_INVALID_ARG, "tree %d: node range [%lld, %lld) is empty or too large",
@@ -354,11 +354,7 @@ ml2_status ml2_load_ensemble(const ml2_ensemble_desc *desc, ml2_ensemble **out) 
   const char *host = nullptr;
   size_t bytes = 0;
   if (ragged) {
-    try {
-      pack_ragged(views, depths, &pk);
-    } catch (const std::bad_alloc &) {
-      return fail(ML2_ERR_OUT_OF_MEMORY, "host staging of the ragged layout failed");
-    }
+    pack_ragged(views, depths, &pk);
     f.num_trees_padded = pk.trees;
     f.records = pk.slots;
     f.depth = pk.depth;
@@ -371,19 +367,15 @@ ml2_status ml2_load_ensemble(const ml2_ensemble_desc *desc, ml2_ensemble **out) 
     f.depth = depth;
     f.rec_bytes = ml2::record_bytes(depth);
     bytes = (size_t)f.num_trees_padded * f.rec_bytes;
-    try {
-      perfect.reset(new char[bytes]);
-      host = perfect.get();
-      ml2::parallel_for(f.num_trees_padded, total_nodes, [&](int64_t t) {
-        char *rec = perfect.get() + (size_t)t * f.rec_bytes;
-        if (t < d.num_trees)
-          pad_tree(views[(size_t)t], depth, rec);
-        else
-          pad_identity_tree(depth, rec);
-      });
-    } catch (const std::bad_alloc &) {
-      return fail(ML2_ERR_OUT_OF_MEMORY, "host staging of %zu bytes failed", bytes);
-    }
+    perfect.reset(new char[bytes]);
+    host = perfect.get();
+    ml2::parallel_for(f.num_trees_padded, total_nodes, [&](int64_t t) {
+      char *rec = perfect.get() + (size_t)t * f.rec_bytes;
+      if (t < d.num_trees)
+        pad_tree(views[(size_t)t], depth, rec);
+      else
+        pad_identity_tree(depth, rec);
+    });
   }
   // The tree table is followed by kTreeSlack zero bytes: chunk staging reads
   // whole register sets, past the end of the last chunk.
@@ -407,6 +399,20 @@ ml2_status ml2_load_ensemble(const ml2_ensemble_desc *desc, ml2_ensemble **out) 
   h->f = f;
   *out = h;
   return ML2_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+const char *ml2_last_error(void) { return g_last_error.c_str(); }
+
+ml2_status ml2_load_ensemble(const ml2_ensemble_desc *desc, ml2_ensemble **out) {
+  try {
+    return load_ensemble(desc, out);
+  } catch (const std::bad_alloc &) {
+    return fail(ML2_ERR_OUT_OF_MEMORY, "ml2_load_ensemble: host memory");
+  }
 }
 
 void ml2_free_ensemble(ml2_ensemble *e) {

@@ -4,6 +4,8 @@ call) with the documented status codes."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -314,3 +316,27 @@ def test_stream_explorer_null_handles():
     assert L.ml2_stream_explorer_reset(None) == ml2.ML2_ERR_INVALID_ARG
     assert L.ml2_stream_explorer_rounds(None) == -1
     L.ml2_stream_explorer_free(None)
+
+
+def test_load_without_host_memory():
+    """A load whose host arrays do not fit returns OUT_OF_MEMORY (no exception
+    leaves the library): 200 million trees under an address-space limit of 4 GiB
+    above what the process holds."""
+    code = """
+import ctypes, resource
+from paper_2411_10764_amd import ml2
+L = ml2.lib()
+held = int(open('/proc/self/statm').read().split()[0]) * resource.getpagesize()
+resource.setrlimit(resource.RLIMIT_AS, (held + (4 << 30),) * 2)
+zero = (ctypes.c_int64 * 4)()
+p = ctypes.addressof(zero)
+d = ml2.ml2_ensemble_desc(200000000, 4, 0.0, p, p, p, p, p, p, None)
+out = ctypes.c_void_p()
+print(L.ml2_load_ensemble(ctypes.byref(d), ctypes.byref(out)), out.value,
+      L.ml2_last_error().decode())
+"""
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=120,
+                       cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    assert r.returncode == 0, r.stderr
+    assert r.stdout.split()[:2] == [str(ml2.ML2_ERR_OUT_OF_MEMORY), "None"], r.stdout
+    assert "memory" in r.stdout
