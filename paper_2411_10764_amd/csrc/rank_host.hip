@@ -45,14 +45,17 @@ WalkWork work_of(const std::vector<TreeView> &views, const RankCodes &codes, con
 }
 
 // Ensembles that are small beside the searches of a row keep the float form
-// alone: what ranking gains is little or nothing (412,590 x 136, 42 trees of
-// depth 4: 53 us against 109; 427,763 x 96, 190 of depth 6: 149 against 155;
-// 16M x 128, 300 of depth 6: 7.84 ms against 7.0), and loading a second form
-// takes longer than that.  In node visits per row, a visit saves 0.28 (0.56
-// where the float walk cannot prefetch its rows), a ragged tree 9, and ranking
-// costs 0.8 per search step and 1 per grid feature.  Trees of depth 9
-// and above leave the float walk few trees per lane or few waves, and are
-// never small (500,000 x 256, 100 of depth 12: 47.3 ms against 1.3).
+// alone, whatever the estimates say: of 970 timed walks of such ensembles over
+// aligned rows ranking won by a tenth in 12 %, by 35 us (412,590 x 136, 42 trees
+// of depth 4: 53 us against 109; 427,763 x 96, 190 of depth 6: 149 against 155;
+// 16M x 128, 300 of depth 6, not small: 7.84 ms against 7.0), and loading a
+// second form takes longer than that.  (Rows loaded a float at a time are
+// another matter: ranking won 80 % of 877 such walks, by 110 us in the median.)
+// In node visits per row, a visit saves 0.28 (0.56 where the float walk cannot
+// prefetch its rows), a ragged tree 9, and ranking costs 0.8 per search step and
+// 1 per grid feature.  Trees of depth 9 and above leave the float walk few trees
+// per lane or few waves, and are never small (500,000 x 256, 100 of depth 12:
+// 47.3 ms against 1.3).
 bool small(const WalkWork &w) {
   if (!w.ragged && w.depth >= 9) return false;
   const bool prefetched = row_kind(true, w.features) == kRowsAhead;
